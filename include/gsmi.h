@@ -267,9 +267,8 @@ gs_status gs_bin_sort(const gs_proj* proj, int32_t n, const uint32_t* vis_idx, c
  *   one pixel (never cleared: zero it before the call)
  *   pair_stats [4] uint64 or NULL (accumulated: zero it before the call):
  *   += number of (pixel, pair) evaluations, of included pairs, of (row, pair)
- *   steps the kernel executed (a row is 16 pixels of a tile row, the unit the
- *   kernel walks pairs in), and of those steps in which at least one pixel
- *   included the pair
+ *   steps the kernel executed (a row is the 16 pixels of one 16-lane row of a
+ *   wave), and of those steps in which at least one pixel included the pair
  *   bg: 3 floats on the HOST
  *   tile_order [T] uint32 or NULL: the order in which workgroups take the
  *   tiles (gs_bin_sort's tile_order, any permutation of 0..T-1, or NULL for

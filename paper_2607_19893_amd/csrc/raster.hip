@@ -1,22 +1,26 @@
 // Rendering phase part 2 (forward alpha blending), the L1 image loss, and the
 // backward phase (pixel replay + per-primitive chain rule).
 //
-// Forward: one 256-thread workgroup per 16x16 tile, one pixel per thread.
-// The tile's sorted pairs are staged through LDS in batches of 256
-// (mean2d, conic+opacity, rgb, footprint half-extents); a workgroup-wide
-// count of finished pixels ends the batch loop early.
+// Forward: one 256-thread workgroup per 16x16 tile, one pixel per thread, each
+// wave an 8x8 quadrant.  The tile's sorted pairs are staged through LDS in batches
+// of 256 (sigma's polynomial about the tile centre, opacity, colour, and the blocks
+// of the tile the footprint can reach); a wave walks the list of the pairs that
+// reach its quadrant, and a workgroup-wide count of finished pixels ends the batch
+// loop early.
 //
-// Backward: same tile/pixel mapping, walking each tile's pairs back to front.
-// Each pixel recovers the transmittance in front of a pair by dividing by
-// (1 - alpha) and keeps the projection of the suffix colour sum on its
-// upstream gradient; per pair, six moment and colour sums are taken over each
-// 16-lane pixel row with DPP, stored in the row's LDS record of the pair,
-// combined over the rows of a wave and over the 4 waves in a fixed order, and
-// written to the pair's slot at its emission position (a primitive's pairs
-// side by side).  Per visible primitive, k_slot_sum adds its slots in order
-// -- deterministic, no floating-point atomics in global memory -- and
-// k_project_bwd applies the projection and colour chain rule (geometry in
-// fp64) and writes one compact gradient row.
+// Backward: same tile/pixel mapping, walking each tile's pairs back to front in
+// batches of 64; each 16-lane row of a wave has its own list, of the pairs that
+// reach its 8x2 strip of pixels.  Each pixel recovers the transmittance in front of
+// a pair by dividing by (1 - alpha) and keeps the projection of the suffix colour
+// sum on its upstream gradient; per pair, eight moment and colour sums are taken
+// over each 16-lane row with DPP, stored in the strip's LDS record of the pair,
+// combined over the strips in a fixed order, and written to the pair's slot at its
+// emission position (a primitive's pairs side by side).  Per visible primitive,
+// k_slot_sum adds its slots in order -- deterministic, no floating-point atomics
+// in global memory -- and k_project_bwd applies the projection and colour chain
+// rule (geometry in fp64) and writes one compact gradient row.
+#include <type_traits>
+
 #include "common.h"
 #include "internal.h"
 
@@ -29,84 +33,129 @@ constexpr float kAlphaMax = 0.99f;
 constexpr float kTMin = 1e-4f;
 constexpr float kCutMargin = 1e-3f;   // extra sigma beyond the 1/255 cut-off when bounding a footprint
 
-// One pair's primitive as staged in LDS: 72 bytes in five arrays, every lane
-// of a wave reading the same record (a broadcast):
-//   P (u, v) and Q (A/2, B) in fp64, R = (C/2 in fp64, opacity, hx),
-//   S = (r, g, b, hy), T = (cut, slope) for the row lists (computed once per
-//   staged entry rather than by every wave that tests it).
-// The pixel-space mean and conic are fp32 values held exactly in fp64, so
-// that the quadratic form is evaluated in fp64 without per-pair conversions.
-// hx, hy bound the pixel offsets at which o*exp(-sigma) can reach 1/255: for
-// sigma = d^T Q d / 2 <= s the offsets obey |dx| <= sqrt(2 s C / det Q) and
-// |dy| <= sqrt(2 s A / det Q); s = cut = ln(255 o) + kCutMargin keeps every
-// skipped pair at least 0.1% below the threshold, far outside fp32 rounding.
-// slope = -B/A (fp32) is the vertex of sigma along a pixel row per unit dy.
-struct __align__(16) SplatR {
-    double c2;
-    float o;
-    float hx;
+// One pair's primitive as staged in LDS for the 8x8 walk: 64 bytes, read by a
+// whole wave at one address (a broadcast).
+//   q[0..5]: sigma as a polynomial in the pixel's offset (X, Y) from the tile
+//   centre, in fp64:
+//     sigma = q0 + q1 X + q2 Y + q3 X^2 + q4 XY + q5 Y^2
+//   then the opacity and the colour.
+// fp64 because the terms of sigma cancel for elongated footprints far from their
+// centre (fp32 loses up to ~1e-3 of sigma there); the coefficients are formed
+// once per staged pair from the exact fp32 mean and conic, so a pixel's sigma costs
+// five fused multiply-adds and one conversion.
+struct __align__(16) Splat {
+    double q[6];
+    float o, r, g, b;
 };
 
-template <int NB>
-struct SplatLds {
-    double2 P[NB];
-    double2 Q[NB];
-    SplatR R[NB];
-    float4 S[NB];
-    float2 T[NB];
-};
+// A pair is skipped where sigma < 0.  That can only happen if its conic is not
+// positive definite (kIndefinite): the walks test it in batches that hold such a
+// pair.  The polynomial's rounding is below 1e-10, so a zero of sigma can come out
+// as a tiny negative number.  kCapped marks an opacity above the 0.99 cap of alpha, at
+// which the backward's derivatives of alpha vanish.
+constexpr float kSigmaNeg = -1e-9f;
+constexpr uint32_t kIndefinite = 1u << 16, kCapped = 1u << 17;
 
-template <int NB>
-__device__ __forceinline__ void stage_splat(SplatLds<NB>& L, int k, float2 m, float4 co,
-                                            const float* __restrict__ rgb3) {
-    const float cut = logf(255.0f * co.w) + kCutMargin;
-    const float det = co.x * co.z - co.y * co.y;
-    float hx, hy;
-    if (!(cut > 0.0f)) {
-        hx = hy = -1e30f;                 // opacity below 1/255: no pixel can take it
-    } else if (!(det > 0.0f)) {
-        hx = hy = 1e30f;                  // degenerate conic in fp32: never skip
-    } else {
-        hx = sqrtf(2.0f * cut * co.z / det);
-        hy = sqrtf(2.0f * cut * co.x / det);
+// Fills rec from a pair's mean, conic and colour, relative to the tile centre
+// (xc, yc), and returns the tile's blocks of 8 x BH pixels that hold a pixel centre
+// with sigma <= cut = ln(255 o) + kCutMargin: a block that is left out has no pixel
+// at or above alpha = 1/255.  Bit b is the block of wave b / (8 / BH) (quadrant
+// (w & 1, w >> 1)), counted downwards inside the quadrant; kIndefinite and kCapped
+// come on top.
+//
+// sigma's minimum over a rectangle lies at its centre if that is inside, else on
+// the vertical or horizontal edge line nearest to the centre: along each of the
+// two lines it is at the line's vertex clamped to the rectangle.  In fp32, with
+// the rounding of sigma's terms (bounded by their largest values over the tile)
+// added to the cut.  A conic that is not positive definite reaches every block.
+template <int BH>
+__device__ __forceinline__ uint32_t stage_pair(Splat* rec, float2 m, float4 co, const float* __restrict__ rgb3,
+                                               double xc, double yc) {
+    constexpr int kPer = 8 / BH;                     // blocks of a quadrant
+    constexpr uint32_t kAll = (1u << (4 * kPer)) - 1u;
+    const double du = (double)m.x - xc, dv = (double)m.y - yc;
+    const double qa = 0.5 * (double)co.x, qb = (double)co.y, qc = 0.5 * (double)co.z;
+    const double ax = fma(qa, du, qb * dv), cy = qc * dv;
+    rec->q[0] = fma(du, ax, cy * dv);
+    rec->q[1] = -fma(qa, du, ax);
+    rec->q[2] = -fma(qb, du, 2.0 * cy);
+    rec->q[3] = qa;
+    rec->q[4] = qb;
+    rec->q[5] = qc;
+    rec->o = co.w;
+    rec->r = rgb3[0];
+    rec->g = rgb3[1];
+    rec->b = rgb3[2];
+    constexpr float kLn2 = 0.693147180559945309417f;
+    const float cut = fmaf(__builtin_amdgcn_logf(255.0f * co.w), kLn2, kCutMargin);
+    if (!(cut > 0.0f)) return 0u;              // opacity below 1/255: no pixel can take it
+    const float A = co.x, B = co.y, C = co.z, u = (float)du, v = (float)dv;
+    if (!(A > 0.0f) || !((double)A * C - (double)B * B > 0.0)) {
+        const bool nan = u != u || v != v || (A > 0.0f && (B != B || C != C));
+        return nan ? 0u : kAll | kIndefinite | kCapped;
     }
-    L.P[k] = make_double2((double)m.x, (double)m.y);
-    L.Q[k] = make_double2(0.5 * (double)co.x, (double)co.y);
-    SplatR r;
-    r.c2 = 0.5 * (double)co.z;
-    r.o = co.w;
-    r.hx = hx;
-    L.R[k] = r;
-    L.S[k] = make_float4(rgb3[0], rgb3[1], rgb3[2], hy);
-    L.T[k] = make_float2(cut, co.x > 0.0f ? -co.y * __builtin_amdgcn_rcpf(co.x) : 0.0f);
+    const float sx = -B * __builtin_amdgcn_rcpf(A), sy = -B * __builtin_amdgcn_rcpf(C);
+    const float mx = fabsf(u) + 7.5f, my = fabsf(v) + 7.5f;
+    const float hA = 0.5f * A, hC = 0.5f * C;
+    const float lim = fmaf(1e-6f, hA * mx * mx + fabsf(B) * mx * my + hC * my * my, cut);
+    uint32_t mask = co.w > kAlphaMax ? kCapped : 0u;
+#pragma unroll
+    for (int r = 0; r < 2 * kPer; ++r) {
+        // offsets (splat - pixel) over the block's rows and columns
+        const float ylo = v + (7.5f - (float)(r * BH + BH - 1)), yhi = ylo + (float)(BH - 1);
+        const float dyn = __builtin_amdgcn_fmed3f(0.0f, ylo, yhi);
+        const float bdy = B * dyn, cdy = hC * dyn * dyn, vx = sx * dyn;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const float xlo = c ? u - 7.5f : u + 0.5f, xhi = xlo + 7.0f;
+            const float dxn = __builtin_amdgcn_fmed3f(0.0f, xlo, xhi);
+            const float dyv = __builtin_amdgcn_fmed3f(sy * dxn, ylo, yhi);
+            const float dxv = __builtin_amdgcn_fmed3f(vx, xlo, xhi);
+            const float s1 = fmaf(fmaf(hC, dyv, B * dxn), dyv, hA * dxn * dxn);
+            const float s2 = fmaf(fmaf(hA, dxv, bdy), dxv, cdy);
+            if (fminf(s1, s2) <= lim) mask |= 1u << ((2 * (r / kPer) + c) * kPer + r % kPer);
+        }
+    }
+    return mask;
 }
 
-// Can any pixel centre of the wave's strip [x0,x1] x [y0,y1] reach the cut-off?
-template <int NB>
-__device__ __forceinline__ bool splat_touches(const SplatLds<NB>& L, int k, float x0, float x1, float y0, float y1) {
-    const double2 p = L.P[k];
-    const float u = (float)p.x, v = (float)p.y;        // exact: staged from fp32
-    const float hx = L.R[k].hx, hy = L.S[k].w;
-    return (u + hx >= x0) && (u - hx <= x1) && (v + hy >= y0) && (v - hy <= y1);
-}
+// A pixel's offset from its tile's centre and its products, for the pairs' sigma.
+struct PixelPoly {
+    double X, Y, XX, XY, YY;
+    __device__ __forceinline__ PixelPoly(int x, int y) {
+        X = x - 7.5;
+        Y = y - 7.5;
+        XX = X * X;
+        XY = X * Y;
+        YY = Y * Y;
+    }
+    __device__ __forceinline__ float eval(const Splat& S) const {
+        return (float)fma(S.q[5], YY, fma(S.q[4], XY, fma(S.q[3], XX, fma(S.q[2], Y, fma(S.q[1], X, S.q[0])))));
+    }
+};
 
-// sigma of one (pixel, primitive) pair, in fp64: for elongated footprints far
-// from their centre the three terms of the quadratic form are large and
-// cancel, and fp32 loses up to ~1e-3 of sigma there (the error grows with the
-// conic's condition number).  The offsets are exact in fp64.  Forward and
-// backward both call this on the same staged record, so they take identical
-// decisions.  bdy = B dy and cdy = (C/2) dy are returned for the backward's
-// d sigma / d(u, v).  px, py are the pixel centre.
-#pragma clang fp contract(off)
-__device__ __forceinline__ float splat_sigma(double2 P, double2 Q, double c2, double px, double py, double& ddx,
-                                             double& ddy, double& inner, double& cdy) {
-    ddx = P.x - px;
-    ddy = P.y - py;
-    inner = fma(Q.x, ddx, Q.y * ddy);            // A/2 dx + B dy
-    cdy = c2 * ddy;                              // C/2 dy
-    return (float)fma(ddx, inner, cdy * ddy);
+// Pairs a walk takes per iteration; the lists are padded to a multiple of it.
+constexpr int kPad = 4;
+
+// The list of the nb staged pairs that reach quadrant w, in order, as byte
+// offsets of their records; padded with the offset of record GS_BLOCK.  One wave
+// builds and reads its own list.
+__device__ __forceinline__ uint32_t quad_list(const uint8_t* quad, uint32_t* list, uint32_t nb, int w) {
+    const int lane = lane_id();
+    const uint64_t lt = lanemask_lt();
+    uint32_t n = 0;
+    for (uint32_t c = 0; c < nb; c += GS_WAVE) {
+        const bool on = (quad[c + lane] >> w) & 1u;
+        const uint64_t m = __ballot(on);
+        if (on) list[n + popc64(m & lt)] = (uint32_t)((c + lane) * sizeof(Splat));
+        n += popc64(m);
+    }
+    if (lane < kPad) list[n + lane] = (uint32_t)(GS_BLOCK * sizeof(Splat));
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    return __builtin_amdgcn_readfirstlane(n);
 }
-#pragma clang fp contract(on)
 
 // exp(-sigma) = 2^-t with t = sigma log2(e) carried as hi + lo (log2(e)
 // split into an fp32 head and tail; hi = sigma * head rounded, lo its exact
@@ -126,72 +175,6 @@ __device__ __forceinline__ float exp_neg(float sigma) {
     return __builtin_amdgcn_exp2f(-hi) * fmaf(-lo, kLn2, 1.0f);
 }
 
-
-// Row-wise lists: each 16-lane row of a wave (one pixel row of the tile)
-// keeps its own ascending list of the batch entries whose footprint reaches
-// that row's pixel centres (and lie below the row's limit).  The four rows of
-// a wave then walk their lists in lockstep, so an entry costs a quarter of a
-// wave step for every pixel row it reaches instead of a whole step for every
-// 16x4 strip.  cnt[r] receives the length of row r's list.  With REV (one
-// ballot round, NB = 64) each list is stored back to front, so that a walk
-// from the last entry to the first reads positions 0, 1, 2, ...
-//
-// An entry reaches row y if sigma <= s somewhere on the row's segment of
-// pixel centres [x0, x1] (s = cut = ln(255 o) + kCutMargin as for hx, hy):
-// the footprint box is tested first, then sigma at the quadratic's vertex dx =
-// slope dy (slope = -B/A in fp32) clamped to the segment's offsets [u - x1,
-// u - x0], in fp64 (the staged values are exact).  Off the exact vertex by the
-// slope's rounding (a few 1e-7 relative), sigma there exceeds the segment's
-// minimum by at most about 4e-13 (B^2 / det), i.e. 4e-13 times the squared
-// axis ratio of the footprint: inside the 1e-3 margin up to ratios near 5e4,
-// where the fp32 conic itself has lost its accuracy.  Any pixel of a skipped
-// row stays below the 1/255 threshold.
-template <int NB, bool REV = false>
-__device__ __forceinline__ void compact_rows(const SplatLds<NB>& L, int nb, float x0, float x1, float y0,
-                                             const uint32_t* lim, uint8_t (*list)[NB], uint32_t* cnt) {
-    static_assert(!REV || NB == GS_WAVE, "a list is reversed within its one ballot round");
-    const int lane = lane_id();
-    const uint64_t lt = lanemask_lt();
-#pragma unroll
-    for (int q = 0; q < 4; ++q) cnt[q] = 0;
-#pragma unroll
-    for (int r = 0; r < NB / GS_WAVE; ++r) {
-        const int k = r * GS_WAVE + lane;
-        const bool valid = k < nb;
-        const int kk = valid ? k : 0;
-        const double2 p = L.P[kk];
-        const double2 qd = L.Q[kk];
-        const SplatR R = L.R[kk];
-        const float u = (float)p.x, v = (float)p.y;
-        const float hx = R.hx, hy = L.S[kk].w;
-        const bool bx = valid && (u + hx >= x0) && (u - hx <= x1);
-        const float2 cs = L.T[kk];
-        const double cut = (double)cs.x;
-        const bool convex = qd.x > 0.0;                      // A > 0 for every projected conic; else no row test
-        const double slope = (double)cs.y;                   // vertex offset per unit dy: -B / A (0 unless A > 0)
-        const double dlo = p.x - (double)x1, dhi = p.x - (double)x0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float y = y0 + (float)q;
-            const double dy = p.y - (double)y;
-            const double dx = fmin(fmax(slope * dy, dlo), dhi);
-            const double smin = dx * fma(qd.x, dx, qd.y * dy) + R.c2 * dy * dy;
-            const bool t = bx && (uint32_t)k < lim[q] && (v + hy >= y) && (v - hy <= y) && (smin <= cut || !convex);
-            const uint64_t m = __ballot(t);
-            if (t) list[q][REV ? popc64(m) - 1u - popc64(m & lt) : cnt[q] + popc64(m & lt)] = (uint8_t)k;
-            cnt[q] += popc64(m);
-        }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// The value of a wave-uniform per-row quantity for this lane's row.
-__device__ __forceinline__ uint32_t for_row(const uint32_t* v, int row) {
-    return row == 0 ? v[0] : (row == 1 ? v[1] : (row == 2 ? v[2] : v[3]));
-}
-
 // |a - t| and the sign of a - t scaled by inv (0 for a tie): one L1 term and its derivative.
 __device__ __forceinline__ float l1_elem(float a, float t, float inv, float& dl) {
     const float d = a - t;
@@ -207,106 +190,123 @@ __device__ __forceinline__ uint32_t dispatch_tile(const uint32_t* __restrict__ t
     return tile_order ? tile_order[blockIdx.x] : blockIdx.x;
 }
 
+// Position of this thread's pixel in its tile: wave w renders the 8x8 quadrant
+// (w & 1, w >> 1), lane l its pixel (l & 7, l >> 3).
+__device__ __forceinline__ int quad_x(int tid) { return ((tid >> 6) & 1) * 8 + (tid & 7); }
+__device__ __forceinline__ int quad_y(int tid) { return (tid >> 7) * 8 + ((tid >> 3) & 7); }
+
+// What bounds it is VALU issue: about 28 instructions per (wave, pair) step, 26 of
+// them per pixel (sigma 6, the exponential 6, blending 14).  An 8x8 block takes more
+// steps than lists per 16x1 row of the tile did (their rows found 54% of the lanes
+// included, a block 34%), but a wave-uniform list needs no per-row lockstep, no list
+// building per row and no per-pair address arithmetic, and sigma as a polynomial no
+// per-pair offsets, so a step got shorter by more: 7.8e7 -> 5.4e7 VALU a view on a
+// 1M-primitive 1080p room.  Four pairs an iteration keep four records' loads and
+// footprints in flight beside the serial T chain; their registers allow six waves per
+// SIMD, which measured better than two pairs at eight waves, most of all where few tiles
+// leave a wave or two per SIMD (256 tiles: 34 us against 39).  Measured, 16x1 rows
+// before and this: room 139 -> 105 us, 3840x2160 render of 500k primitives 305 -> 217,
+// 475 tiles of 400x304 66 -> 38, 256 tiles of 256x256 50 -> 35.
+//
 // LOSS: the L1 loss of the view is taken in the same pass (the image loss of
 // the view, Section 2.1): each pixel compares its three fp32 channels with
 // the target exactly as k_loss_l1 does, writes dL/dimg, and each tile leaves
 // its sum of |img - target| in loss_partial[tile] for k_loss_final.
 template <bool STATS, bool LOSS>
-__global__ void __launch_bounds__(GS_BLOCK, STATS ? 5 : 7) k_raster_fwd(
+__global__ void __launch_bounds__(GS_BLOCK, STATS ? 5 : 6) k_raster_fwd(
     const uint32_t* __restrict__ tile_order, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ vals,
     const float2* __restrict__ mean2d, const float4* __restrict__ conic_op, const float* __restrict__ rgb, int32_t W,
     int32_t H, int32_t TX, float bg0, float bg1, float bg2, float* __restrict__ img, float* __restrict__ final_T,
     uint32_t* __restrict__ n_contrib,
     uint8_t* __restrict__ active, unsigned long long* __restrict__ pair_stats, const float* __restrict__ target,
     float inv_total, float* __restrict__ dL, float* __restrict__ loss_partial) {
-    __shared__ SplatLds<GS_BLOCK> L;
-    // entries some pixel included (active flags): every including lane stores 1 to
-    // the entry's byte, plain stores of one value (LDS atomics on one word from a
-    // whole row serialize)
-    __shared__ uint8_t s_hit[GS_BLOCK];
-    __shared__ uint8_t s_list[4][4][GS_BLOCK];
+    __shared__ Splat L[GS_BLOCK + 1];                    // the last record blends nothing: it pads the lists
+    __shared__ uint8_t s_quad[GS_BLOCK];                 // quadrants each staged pair can reach
+    __shared__ uint8_t s_hit[GS_BLOCK + 1];              // pairs some pixel included (active flags)
+    __shared__ __align__(16) uint32_t s_list[4][GS_BLOCK + kPad];  // per wave: its pairs' records, as offsets into L
     __shared__ uint32_t s_stat[4][4];
     const uint32_t tile = dispatch_tile(tile_order);
     if (tile >= gridDim.x) return;
     const int tid = threadIdx.x;
-    const int w = tid / GS_WAVE;
+    const int w = __builtin_amdgcn_readfirstlane(tid / GS_WAVE);
     const int lane = lane_id();
-    const int row = lane >> 4;
     const int tx = (int)tile % TX, ty = (int)tile / TX;
-    const int px = tx * GS_TILE + (tid % GS_TILE);
-    const int py = ty * GS_TILE + (tid / GS_TILE);
+    const int px = tx * GS_TILE + quad_x(tid);
+    const int py = ty * GS_TILE + quad_y(tid);
     const bool inside = px < W && py < H;
-    const double fx = px + 0.5, fy = py + 0.5;
-    // pixel-centre bounds of this wave's 16x4 strip
-    const float wx0 = tx * GS_TILE + 0.5f, wx1 = wx0 + 15.0f;
-    const float wy0 = ty * GS_TILE + 4 * w + 0.5f;
+    const double xc = tx * GS_TILE + 8, yc = ty * GS_TILE + 8;
+    const PixelPoly P(quad_x(tid), quad_y(tid));
     const uint32_t start = ranges[2 * tile], end = ranges[2 * tile + 1];
-    float T = 1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
+    // T, negated once the pixel is finished: every later T (1 - alpha) is then below kTMin
+    float T = inside ? 1.0f : -1.0f;
+    float c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
     uint32_t last = 0, n_inc = 0, term_at = 0, w_iter = 0, w_hit = 0;
-    bool done = !inside, terminated = false;
+    if (tid < 16) reinterpret_cast<float*>(&L[GS_BLOCK])[tid] = 0.0f;
     // the ids of the next batch load while this one is walked
     uint32_t g = start + tid < end ? vals[start + tid] : 0u;
     for (uint32_t bs = start; bs < end; bs += GS_BLOCK) {
-        if (__syncthreads_count(done) == GS_BLOCK) break;
+        if (__syncthreads_count(T < 0.0f) == GS_BLOCK) break;
         const uint32_t j = bs + tid;
         const uint32_t gj = g;
-        if (j < end) stage_splat(L, tid, mean2d[gj], conic_op[gj], rgb + 3 * (size_t)gj);
+        uint32_t quad = 0u;
+        if (j < end) quad = stage_pair<8>(&L[tid], mean2d[gj], conic_op[gj], rgb + 3 * (size_t)gj, xc, yc);
         if (j + GS_BLOCK < end) g = vals[j + GS_BLOCK];
+        s_quad[tid] = (uint8_t)quad;
         s_hit[tid] = 0;
-        __syncthreads();
-        const int nb = (int)min((uint32_t)GS_BLOCK, end - bs);
-        // rows whose 16 pixels are all finished take no entries
-        const uint64_t live = __ballot(!done);
-        uint32_t lim[4], nl[4] = {0u, 0u, 0u, 0u};
+        const bool check = __syncthreads_or((int)(quad & kIndefinite));
+        if (__ballot(T > 0.0f) != 0ull) {
+            const uint32_t n_list = quad_list(s_quad, s_list[w], min((uint32_t)GS_BLOCK, end - bs), w);
+            uint32_t lk = 0xFFFFFFFFu;      // record offset of the pixel's last included pair of this batch
+            auto walk = [&](auto checked) {
+                constexpr bool CHECK = decltype(checked)::value;
+                // kPad pairs at a time: their records load together and their footprints are
+                // evaluated side by side; the blending then takes them in order
+                for (uint32_t i0 = 0; i0 < n_list; i0 += kPad) {
+                    uint32_t ats[kPad];
+                    __builtin_memcpy(ats, __builtin_assume_aligned(&s_list[w][i0], 4 * kPad), sizeof(ats));
+                    uint32_t hit = 0u;      // of the kPad pairs, those some pixel included
 #pragma unroll
-        for (int q = 0; q < 4; ++q) lim[q] = ((live >> (16 * q)) & 0xFFFFull) ? (uint32_t)GS_BLOCK : 0u;
-        if (live) compact_rows(L, nb, wx0, wx1, wy0, lim, s_list[w], nl);
-        const uint32_t my_n = for_row(nl, row);
-        // the counts come from ballots, so every lane holds the same values
-        const uint32_t steps = __builtin_amdgcn_readfirstlane(max(max(nl[0], nl[1]), max(nl[2], nl[3])));
-        uint64_t live_w = live;     // lanes not yet done, kept as a scalar mask
-        for (uint32_t jj = 0; jj < steps; ++jj) {
-            if (live_w == 0ull) break;
-            const bool act = jj < my_n;
-            // the list read needs no branch (every byte indexes the 256-entry batch), but
-            // past the row's count the byte is stale and may name a slot this batch never
-            // staged, whose colour could be Inf or NaN (0 * Inf poisons the sums): such
-            // lanes take entry 0, which every batch stages
-            const int k_list = s_list[w][row][jj];
-            const int k = act ? k_list : 0;
-            const SplatR R = L.R[k];
-            double ddx, ddy, inner, cdy;
-            const float sigma = splat_sigma(L.P[k], L.Q[k], R.c2, fx, fy, ddx, ddy, inner, cdy);
-            const float alpha = fminf(kAlphaMax, R.o * exp_neg(sigma));
-            bool ok = act && !done && !(sigma < 0.0f) && !(alpha < kAlphaMin);
-            const float Tn = T * (1.0f - alpha);
-            const bool term = ok && (Tn < kTMin);
-            const uint32_t pos = bs - start + (uint32_t)k;
-            if (STATS && term) term_at = pos;
-            terminated = terminated || term;
-            done = done || term;
-            // the terminating lanes, as ballots of the comparisons themselves (a ballot of
-            // a compare is its lane mask; a ballot of a combined flag costs two VALU ops)
-            live_w &= ~(__builtin_amdgcn_ballot_w64(act) & live_w & __builtin_amdgcn_ballot_w64(!(sigma < 0.0f)) &
-                        __builtin_amdgcn_ballot_w64(!(alpha < kAlphaMin)) & __builtin_amdgcn_ballot_w64(Tn < kTMin));
-            ok = ok && !term;
-            const float4 col = L.S[k];
-            const float wgt = ok ? alpha * T : 0.0f;
-            c0 = fmaf(wgt, col.x, c0);
-            c1 = fmaf(wgt, col.y, c1);
-            c2 = fmaf(wgt, col.z, c2);
-            T = ok ? Tn : T;
-            last = ok ? pos + 1u : last;
-            if (STATS) {
-                n_inc += ok ? 1u : 0u;
-                const uint64_t am = __ballot(act), om = __ballot(ok);
+                    for (int i = 0; i < kPad; ++i) {
+                        const uint32_t at = ats[i];
+                        const Splat& S = *reinterpret_cast<const Splat*>(reinterpret_cast<const char*>(L) + at);
+                        const float sigma = P.eval(S);
+                        float al = fminf(kAlphaMax, S.o * exp_neg(sigma));
+                        uint64_t ok_mask = __builtin_amdgcn_ballot_w64(!(al < kAlphaMin));
+                        bool ok = !(al < kAlphaMin);
+                        if (CHECK) {
+                            ok_mask &= __builtin_amdgcn_ballot_w64(!(sigma < kSigmaNeg));
+                            ok = ok & !(sigma < kSigmaNeg);
+                        }
+                        al = ok ? al : 0.0f;
+                        const float Tn = T * (1.0f - al);
+                        const bool go = !(Tn < kTMin);       // stop in front of a pair that would leave less
+                        if (STATS && !go && T > 0.0f) term_at = bs - start + at / (uint32_t)sizeof(Splat) + 1u;
+                        const float wgt = go ? al * T : 0.0f;
+                        c0 = fmaf(wgt, S.r, c0);
+                        c1 = fmaf(wgt, S.g, c1);
+                        c2 = fmaf(wgt, S.b, c2);
+                        T = go ? Tn : -fabsf(T);
+                        ok = ok && go;
+                        lk = ok ? at : lk;
+                        hit |= (ok_mask & __builtin_amdgcn_ballot_w64(go)) != 0ull ? 1u << i : 0u;
+                        if (STATS && i0 + i < n_list) {
+                            n_inc += ok ? 1u : 0u;
+                            const uint64_t om = __ballot(ok);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    w_iter += ((am >> (16 * q)) & 0xFFFFull) ? 1u : 0u;
-                    w_hit += ((om >> (16 * q)) & 0xFFFFull) ? 1u : 0u;
+                            for (int q = 0; q < 4; ++q) w_hit += ((om >> (16 * q)) & 0xFFFFull) ? 1u : 0u;
+                            w_iter += 4u;
+                        }
+                    }
+                    // every wave that stores here stores the same value
+                    if (active != nullptr && lane < kPad && ((hit >> lane) & 1u)) s_hit[s_list[w][i0 + lane] / (uint32_t)sizeof(Splat)] = 1;
+                    if (__ballot(T > 0.0f) == 0ull) break;
                 }
-            }
-            if (active != nullptr && ok) s_hit[k] = 1;
+            };
+            if (check)
+                walk(std::true_type{});
+            else
+                walk(std::false_type{});
+            last = lk != 0xFFFFFFFFu ? bs - start + lk / (uint32_t)sizeof(Splat) + 1u : last;
         }
         __syncthreads();
         if (active && j < end && s_hit[tid]) active[gj] = 1;
@@ -314,7 +314,7 @@ __global__ void __launch_bounds__(GS_BLOCK, STATS ? 5 : 7) k_raster_fwd(
     if (STATS) {
         // entries the per-pixel definition examines: up to and including the
         // terminating one, else the whole list
-        const uint32_t n_eval = !inside ? 0u : (terminated ? term_at + 1u : end - start);
+        const uint32_t n_eval = !inside ? 0u : (T < 0.0f ? term_at : end - start);
         const uint32_t e = wave_sum_u32(n_eval), i = wave_sum_u32(n_inc);
         if (lane_id() == 0) {
             s_stat[0][w] = e;
@@ -327,6 +327,7 @@ __global__ void __launch_bounds__(GS_BLOCK, STATS ? 5 : 7) k_raster_fwd(
             atomicAdd(&pair_stats[tid], (unsigned long long)s_stat[tid][0] + s_stat[tid][1] + s_stat[tid][2] +
                                             s_stat[tid][3]);
     }
+    T = fabsf(T);
     float lsum = 0.0f;
     if (inside) {
         const size_t HW = (size_t)W * H, p = (size_t)py * W + px;
@@ -449,11 +450,10 @@ __global__ void __launch_bounds__(GS_BLOCK) k_loss_final(const float* __restrict
 
 constexpr int kG = 9;   // du dv dA dB dC dopacity dr dg db
 constexpr int kSlot = 12;          // floats per pair slot (9 used, padded for 16-byte stores)
-constexpr int kRowSums = 6;        // per-row sums: sum ds, sum ds dx, sum ds dx^2, three colour sums
-// Pairs staged per batch: one per lane, so that after the walk each wave adds
-// its four rows' sums of entry k in lane k.  The per-row sums (16 rows x 6
-// floats per staged pair, 24 KB) dominate the workgroup's LDS.
-constexpr int kBwdBatch = GS_WAVE;
+constexpr int kBwdBatch = GS_WAVE;    // pairs walked between two combinations of the strips' sums
+constexpr int kBwdPad = 2;            // pairs per iteration of the walk
+constexpr int kStrips = 4;            // 8x2 strips of a wave's 8x8 quadrant, one per 16-lane row
+constexpr int kSums = 8;              // floats a strip keeps per pair
 
 // Per pixel, walking back to front: T is recovered in front of each included
 // pair as T / (1 - alpha), and instead of the three suffix colour sums S_c
@@ -461,8 +461,6 @@ constexpr int kBwdBatch = GS_WAVE;
 // keeps their projection gS = sum_c dL/dC_c S_c on its upstream gradient,
 // which is all that d alpha needs:
 //   dL/dalpha = T_k (g . rgb) - gS / (1 - alpha),  gS += alpha T_k (g . rgb).
-// Each 16-lane pixel row walks its own list of the batch (compact_rows),
-// back to front, only up to the last pair any of its pixels included.
 //
 // The 2D gradient of a pair is linear in moments of ds = dL/dsigma over its
 // pixels: with sigma = (A dx^2 + 2B dx dy + C dy^2) / 2 and (dx, dy) the offset
@@ -471,42 +469,96 @@ constexpr int kBwdBatch = GS_WAVE;
 //   dL/dA = m_xx / 2,  dL/dB = m_xy,  dL/dC = m_yy / 2,  dL/dopacity = -m / o,
 // with m = sum ds, m_x = sum ds dx, m_xy = sum ds dx dy and so on (the opacity
 // line because ds = -dL/dalpha * o e^-sigma below the 0.99 cap, and both are 0
-// at it).  A pixel row shares dy, so a row needs only m, m_x and m_xx (plus
-// the three colour sums) over its lanes.  A row visits an entry at most once
-// per batch, so two lanes of the row (one holding the moment sums, one the
-// colour sums) store the six sums with plain LDS writes into the row's own
-// record of that entry (no atomics); after the walk lane k of each
-// wave scales its four rows' records of entry k by their dy and adds them,
-// and the four waves' results are added in a fixed order.  A pair slot holds
+// at it).  Each 16-lane row of a wave renders an 8x2 strip of pixels and walks its
+// own list of the batch.  The strip's two pixel rows lie h = +-1/2 below and above
+// its middle, h^2 = 1/4, so eight sums hold all moments: of ds, ds dx, ds dx^2,
+// ds h, ds dx h and the three colour terms; with c the splat's offset from the
+// strip's middle row, m_y = c m - m_h, m_xy = c m_x - m_xh and
+// m_yy = c^2 m - 2 c m_h + m / 4.  A strip takes a pair at most once per batch, so
+// its sums go to the (strip, pair) record with plain LDS writes; after the walk
+// four threads per pair add the 16 strips' records in a fixed order.  A pair slot holds
 // (m_x, m_y, m_xx, m_xy, m_yy, m, colour); k_project_bwd expands it with the
 // conic once per primitive.
-__global__ void __launch_bounds__(GS_BLOCK) k_raster_bwd(
+//
+// What bounds it is VALU issue: 55 instructions per (wave, pair) step, 24 of them for
+// the eight sums.  The strip is 8x2 because it weighs the steps against the sums:
+// 16x1 rows need six sums but 1.26 times the steps, 4x4 blocks nine for 0.93 times, 8x8
+// blocks nine over 64 lanes for 1.33 times.  The sums are DPP additions because nothing
+// else here is cheaper: the 32-bit matrix product does not run beside other waves' VALU
+// on this chip (one 16x16x4 product costs 34 cycles of it, and the four products that
+// sum 64 pixels took the walk from 209 to 293 us), and an LDS float add costs 3 cycles a
+// lane.  The records (33 KB) allow four workgroups per CU.  Measured, 16x1 rows with a
+// butterfly each before and this: 1M-primitive 1080p room (with the overlapped commit)
+// 264 -> 213 us, 3M walk-through 151 -> 92, 200k ring at 720p 169 -> 132, 60k ring at
+// 651x433 143 -> 80, 10k box at 256x256 82 -> 46.
+
+// The sums of a..h over each 16-lane row, in 16 DPP additions: the halves of two
+// values are added into the two halves of one register, then the quarters of two
+// such registers into the quarters of one; two steps inside each quarter finish.
+// Returns quarter by quarter a, c, b, d in the even lanes and e, g, f, h in the odd
+// ones.  A DPP source must have been written at least two instructions earlier
+// (s_nop where the order does not see to it).
+__device__ __forceinline__ float row_sum8(float a, float b, float c, float d, float e, float f, float g, float h,
+                                          bool odd) {
+    asm("s_nop 1\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %0, %4, %4 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %1, %1, %1 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %1, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %2, %2, %2 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %2, %6, %6 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %3, %3, %3 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %3, %7, %7 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %0, %0, %0 row_shl:4 row_mask:0xf bank_mask:0x5\n\t"
+        "v_add_f32_dpp %0, %1, %1 row_shr:4 row_mask:0xf bank_mask:0xa\n\t"
+        "v_add_f32_dpp %2, %2, %2 row_shl:4 row_mask:0xf bank_mask:0x5\n\t"
+        "v_add_f32_dpp %2, %3, %3 row_shr:4 row_mask:0xf bank_mask:0xa\n\t"
+        "s_nop 0\n\t"
+        "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %2, %2, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 0\n\t"
+        "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %2, %2, %2 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+        : "+&v"(a), "+&v"(c), "+&v"(e), "+&v"(g)
+        : "v"(b), "v"(d), "v"(f), "v"(h));
+    return odd ? e : a;
+}
+
+__device__ __forceinline__ float quad_add(float v) {
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, true));
+}
+
+__global__ void __launch_bounds__(GS_BLOCK, 4) k_raster_bwd(
     const uint32_t* __restrict__ tile_order, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ vals,
     const float2* __restrict__ mean2d, const float4* __restrict__ conic_op, const float* __restrict__ rgb, int32_t W,
     int32_t H, int32_t TX, float bg0,
     float bg1, float bg2, const float* __restrict__ final_T, const uint32_t* __restrict__ n_contrib,
     const float* __restrict__ dL_dimg, const uint32_t* __restrict__ pair_emit, float* __restrict__ slots) {
-    __shared__ SplatLds<kBwdBatch> L;
-    // [wave][row][sum][entry]; after the walk a wave's part holds its 9 combined
-    // sums per entry, [q][entry]
-    __shared__ float s_row[4][4][kRowSums][kBwdBatch];
-    __shared__ uint8_t s_list[4][4][kBwdBatch];
-    __shared__ uint32_t s_max;
-    static_assert(kG * kBwdBatch <= 4 * kRowSums * kBwdBatch, "combined sums fit a wave's row records");
+    // record and sums kBwdBatch belong to a pair that blends nothing: it pads the lists
+    __shared__ Splat L[kBwdBatch + 1];
+    __shared__ __align__(16) float s_sum[4 * kStrips][kBwdBatch + 1][kSums];
+    __shared__ float s_u[kBwdBatch + 1], s_v[kBwdBatch];      // splat centres, relative to the tile's
+    __shared__ __align__(4) uint16_t s_list[4 * kStrips][kBwdBatch + kBwdPad];   // per strip: byte offsets of its pairs' sums
+    __shared__ uint32_t s_emit[kBwdBatch];
+    __shared__ uint32_t s_max[4];
+    __shared__ uint32_t s_special;
+    __shared__ uint16_t s_mask[kBwdBatch];
+    constexpr uint32_t kStep = kSums * sizeof(float);          // a list entry is pair k's k * kStep
+    static_assert(sizeof(Splat) == 2 * kStep, "a record lies at twice its sums' offset");
     const uint32_t tile = dispatch_tile(tile_order);
     if (tile >= gridDim.x) return;
     const int tid = threadIdx.x;
-    const int w = tid / GS_WAVE;
+    const int w = __builtin_amdgcn_readfirstlane(tid / GS_WAVE);
     const int lane = lane_id();
-    const int row = lane >> 4;
+    const int strip = lane >> 4;
     const int tx = (int)tile % TX, ty = (int)tile / TX;
-    const int px = tx * GS_TILE + (tid % GS_TILE);
-    const int py = ty * GS_TILE + (tid / GS_TILE);
+    const int px = tx * GS_TILE + quad_x(tid);
+    const int py = ty * GS_TILE + quad_y(tid);
     const bool inside = px < W && py < H;
-    const double fx = px + 0.5, fy = py + 0.5;
-    const float wx0 = tx * GS_TILE + 0.5f, wx1 = wx0 + 15.0f;
-    const float wy0 = ty * GS_TILE + 4 * w + 0.5f;
-    const uint32_t start = ranges[2 * tile], end = ranges[2 * tile + 1];
+    const double xc = tx * GS_TILE + 8, yc = ty * GS_TILE + 8;
+    const PixelPoly P(quad_x(tid), quad_y(tid));
+    const uint32_t start = ranges[2 * tile], n = ranges[2 * tile + 1] - start;
     const size_t HW = (size_t)W * H, pix = (size_t)py * W + px;
     float T = inside ? final_T[pix] : 1.0f;
     const uint32_t last = inside ? n_contrib[pix] : 0u;
@@ -514,188 +566,163 @@ __global__ void __launch_bounds__(GS_BLOCK) k_raster_bwd(
     const float gC1 = inside ? dL_dimg[HW + pix] : 0.0f;
     const float gC2 = inside ? dL_dimg[2 * HW + pix] : 0.0f;
     float gS = T * (gC0 * bg0 + gC1 * bg1 + gC2 * bg2);
-    if (tid == 0) s_max = 0;
-    {
-        // a walk reads list bytes past its row's count too (without a branch): every
-        // byte must name an entry of the batch arrays, and every entry must hold
-        // finite values, also before a batch has written them
-        static_assert(sizeof(s_list) == 4 * GS_BLOCK, "one word of the lists per thread");
-        reinterpret_cast<uint32_t*>(&s_list[0][0][0])[tid] = 0u;
-        float4* zs = reinterpret_cast<float4*>(&L);
-        for (int i = tid; i < (int)(sizeof(L) / 16); i += GS_BLOCK) zs[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    }
-    __syncthreads();
-    if (last > 0) atomicMax(&s_max, last);
-    __syncthreads();
-    const uint32_t maxlast = s_max;
-    const bool hi_half = (lane & 8) != 0;       // high half of the lane's 16-lane row
-    const int q_half = hi_half ? 3 : 0;         // the half's three sums in a row record
-    // the colour sums of entry k sit at index k ^ 16: the row's two storing lanes
-    // (same entry, records 3 x 64 floats apart) then hit different banks
-    const int k_half = hi_half ? 16 : 0;
-    // largest n_contrib of each pixel row of this wave (wave-uniform values)
+    // largest n_contrib of each strip of the wave, and of the tile
     uint32_t rl = last;
 #pragma unroll
     for (int d = 8; d >= 1; d >>= 1) rl = max(rl, (uint32_t)__shfl_xor((int)rl, d, GS_WAVE));
-    uint32_t row_last[4];
+    uint32_t strip_last[kStrips], wl = 0u;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) row_last[q] = (uint32_t)__builtin_amdgcn_readlane((int)rl, 16 * q);
-    const uint32_t n = end - start;
-    for (int64_t be = n; be > 0; be -= kBwdBatch) {
-        const uint32_t bs = (uint32_t)(be > kBwdBatch ? be - kBwdBatch : 0);
-        const uint32_t cnt = (uint32_t)be - bs;
-        const bool work = bs < maxlast;
-        const uint32_t last_b = last > bs ? last - bs : 0u;    // the pixel's entries in this batch: k < last_b
-        if ((uint32_t)tid < cnt && work) {
-            const uint32_t g = vals[start + bs + tid];
-            stage_splat(L, tid, mean2d[g], conic_op[g], rgb + 3 * (size_t)g);
+    for (int q = 0; q < kStrips; ++q) {
+        strip_last[q] = (uint32_t)__builtin_amdgcn_readlane((int)rl, 16 * q);
+        wl = max(wl, strip_last[q]);
+    }
+    if (lane == 0) s_max[w] = wl;
+    if (tid < 16) reinterpret_cast<float*>(&L[kBwdBatch])[tid] = 0.0f;
+    if (tid == 16) s_u[kBwdBatch] = 0.0f;
+    if (tid < 4 * kStrips * kBwdPad) s_list[tid / kBwdPad][kBwdBatch + tid % kBwdPad] = (uint16_t)(kBwdBatch * kStep);
+    __syncthreads();
+    const uint32_t maxlast = max(max(s_max[0], s_max[1]), max(s_max[2], s_max[3]));
+    const float xj = (float)quad_x(tid) - 7.5f, h = (lane & 8) ? 0.5f : -0.5f;
+    // where this lane stores its sum: row_sum8 leaves sum (bank, odd) in every lane of a bank's parity
+    const bool odd = (lane & 1) != 0;
+    const int bank = (lane >> 2) & 3;
+    char* const my_sums = reinterpret_cast<char*>(&s_sum[w * kStrips + strip][0][bank + (odd ? 4 : 0)]);
+    if (n == 0) return;
+    for (int32_t gs = (int32_t)((n - 1) / GS_BLOCK * GS_BLOCK); gs >= 0; gs -= GS_BLOCK) {
+        // the next 256 pairs' primitives, one per thread; wave b then stages batch b
+        const uint32_t pos = (uint32_t)gs + tid;
+        float2 m = make_float2(0.0f, 0.0f);
+        float4 co = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        float cr[3] = {0.0f, 0.0f, 0.0f};
+        const uint32_t emit = pos < n ? pair_emit[start + pos] : 0u;
+        if (pos < n && pos < maxlast) {
+            const uint32_t g = vals[start + pos];
+            m = mean2d[g];
+            co = conic_op[g];
+            cr[0] = rgb[3 * (size_t)g];
+            cr[1] = rgb[3 * (size_t)g + 1];
+            cr[2] = rgb[3 * (size_t)g + 2];
         }
-        if (work) {
-            // rows that never take an entry leave its record at zero
-            float4* z = reinterpret_cast<float4*>(&s_row[w][0][0][0]);
-#pragma unroll
-            for (int i = 0; i < 4 * kRowSums * kBwdBatch / 4 / GS_WAVE; ++i)
-                z[i * GS_WAVE + lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        }
-        __syncthreads();
-        uint32_t lim[4], nl[4] = {0u, 0u, 0u, 0u};
-        bool any = false;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            lim[q] = row_last[q] > bs ? row_last[q] - bs : 0u;
-            any = any || lim[q] > 0u;
-        }
-        if (work && any) compact_rows<kBwdBatch, true>(L, (int)cnt, wx0, wx1, wy0, lim, s_list[w], nl);
-        const uint32_t my_n = for_row(nl, row);
-        // the counts come from ballots, so every lane holds the same values
-        uint32_t nls[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) nls[q] = __builtin_amdgcn_readfirstlane(nl[q]);
-        const uint32_t steps = __builtin_amdgcn_readfirstlane(max(max(nls[0], nls[1]), max(nls[2], nls[3])));
-        for (uint32_t jj = 0; jj < steps; ++jj) {
-            const bool act = jj < my_n;
-            // act's lanes from the rows' list lengths, in scalar registers
-            uint64_t act_mask = 0ull;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) act_mask |= jj < nls[q] ? 0xFFFFull << (16 * q) : 0ull;
-            // the lists are stored back to front; past the row's count the byte is stale
-            // (or cleared) but names an entry whose values are finite, and the lane is
-            // not ok
-            const int k = s_list[w][row][jj];
-            const SplatR R = L.R[k];
-            double ddx, ddy, inner, cdy;
-            const float sigma = splat_sigma(L.P[k], L.Q[k], R.c2, fx, fy, ddx, ddy, inner, cdy);
-            const float e = exp_neg(sigma);
-            const float gv = R.o * e;
-            const float alpha = fminf(kAlphaMax, gv);
-            const bool ok = act & ((uint32_t)k < last_b) & !(sigma < 0.0f) & !(alpha < kAlphaMin);
-            // the lanes of ok, as ballots of the comparisons themselves (a ballot of a
-            // compare is its lane mask; a ballot of a combined flag costs two VALU ops)
-            const uint64_t mask = act_mask & __builtin_amdgcn_ballot_w64((uint32_t)k < last_b) &
-                                  __builtin_amdgcn_ballot_w64(!(sigma < 0.0f)) &
-                                  __builtin_amdgcn_ballot_w64(!(alpha < kAlphaMin));
-            if (mask == 0ull) continue;
-            const float4 col = L.S[k];
-            // a lane that is not ok takes alpha = 0: 1 / (1 - 0) = 1 leaves its T as it
-            // is, and its weight and d sigma are 0
-            const float a_ok = ok ? alpha : 0.0f;
-            const float inv_om = __builtin_amdgcn_rcpf(1.0f - a_ok);
-            const float Tk = T * inv_om;
-            const float gcol = gC0 * col.x + gC1 * col.y + gC2 * col.z;
-            const float dalpha = Tk * gcol - gS * inv_om;
-            const float wgt = a_ok * Tk;
-            gS = fmaf(wgt, gcol, gS);
-            T = Tk;
-            const float a_geo = gv < kAlphaMax ? a_ok : 0.0f;   // the 0.99 cap stops d/d(opacity, sigma)
-            const float ds = -dalpha * a_geo;
-            const float dsx = ds * (float)ddx;
-            // the six sums over each 16-lane row (all its lanes hold the same entry)
-            // in 18 DPP adds instead of 24: the first stage pairs lane i with lane
-            // 15 - i, the low half of the row keeping the three moment terms and the
-            // high half the three colour terms (each adds its partner's copy of the
-            // term it keeps); three butterfly stages within each half of eight lanes
-            // then leave the moment sums in every low lane and the colour sums in
-            // every high lane
-            const float mo[3] = {ds, dsx, dsx * (float)ddx};
-            const float co[3] = {gC0 * wgt, gC1 * wgt, gC2 * wgt};
-            float gr[3];
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                const float keep = hi_half ? co[q] : mo[q];
-                const float send = hi_half ? mo[q] : co[q];
-                gr[q] = keep + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(send), 0x140, 0xF, 0xF,
-                                                                          true));
+        for (int b = (int)min(3u, (n - 1u - (uint32_t)gs) / kBwdBatch); b >= 0; --b) {
+            const uint32_t bs = (uint32_t)gs + b * kBwdBatch;
+            const uint32_t cnt = min((uint32_t)kBwdBatch, n - bs);
+            if (bs >= maxlast) {
+                // no pixel included any of these
+                if (w == b && (uint32_t)lane < cnt) {
+                    float4* dst = reinterpret_cast<float4*>(slots + (size_t)emit * kSlot);
+                    dst[0] = dst[1] = dst[2] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                }
+                continue;
             }
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                gr[q] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(gr[q]), 0xB1, 0xF, 0xF, true));
-                gr[q] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(gr[q]), 0x4E, 0xF, 0xF, true));
-                gr[q] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(gr[q]), 0x141, 0xF, 0xF, true));
-                // keep the last add in front of the branch (all lanes active), where
-                // it folds into the DPP instruction
-                asm volatile("" : "+v"(gr[q]));
+            if (w == b) {
+                uint32_t mask = 0u;
+                if ((uint32_t)lane < cnt && pos < maxlast) mask = stage_pair<2>(&L[lane], m, co, cr, xc, yc);
+                s_u[lane] = (float)((double)m.x - xc);
+                s_v[lane] = (float)((double)m.y - yc);
+                s_mask[lane] = (uint16_t)mask;
+                s_emit[lane] = emit;
+                const uint64_t sp = __ballot((mask & (kIndefinite | kCapped)) != 0u);
+                if (lane == 0) s_special = sp != 0ull ? 1u : 0u;
             }
-            // lanes 0 and 8 of every row that walks an entry store (moments and colour
-            // sums): a row without a contributing pixel stores zero sums into its
-            // record, which holds zeros (records are cleared per batch and a row
-            // visits an entry once)
-            if ((lane & 7) == 0 && act) {
+            __syncthreads();
+            // the strips' lists, back to front and filled up with the pad; pairs a strip does not take leave zero sums
+            const uint32_t mask = (uint32_t)s_mask[lane] >> (kStrips * w);
+            uint32_t n_list = 0u;
 #pragma unroll
-                for (int q = 0; q < 3; ++q) s_row[w][row][q_half + q][k ^ k_half] = gr[q];
+            for (int q = 0; q < kStrips; ++q) {
+                const bool on = bs + (uint32_t)lane < strip_last[q] && ((mask >> q) & 1u);
+                const uint64_t taken = __ballot(on);
+                const uint32_t nq = popc64(taken), before = popc64(taken & lanemask_lt());
+                s_list[w * kStrips + q][on ? nq - 1u - before : nq + lane - before] =
+                    (uint16_t)((on ? lane : kBwdBatch) * kStep);
+                if (!on) {
+                    float4* z = reinterpret_cast<float4*>(&s_sum[w * kStrips + q][lane][0]);
+                    z[0] = z[1] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                }
+                n_list = max(n_list, nq);
             }
-        }
-        // lane k adds this wave's four row records of entry k: only this wave
-        // wrote them, so a wave-level barrier orders the writes before the reads
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (work) {
-            float acc[kG] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-            const double vk = L.P[lane].y;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float dy = (float)(vk - (double)(wy0 + (float)q));   // the row's common offset
-                const float m = s_row[w][q][0][lane], mx = s_row[w][q][1][lane];
-                const float my = dy * m;
-                acc[0] += mx;
-                acc[1] += my;
-                acc[2] += s_row[w][q][2][lane];
-                acc[3] += dy * mx;
-                acc[4] += dy * my;
-                acc[5] += m;
-                acc[6] += s_row[w][q][3][lane ^ 16];
-                acc[7] += s_row[w][q][4][lane ^ 16];
-                acc[8] += s_row[w][q][5][lane ^ 16];
-            }
+            n_list = __builtin_amdgcn_readfirstlane(n_list);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            float* comb = &s_row[w][0][0][0];
+            // the pixel's pairs of this batch: offsets below last_b
+            const uint32_t last_b = (last > bs ? min(last - bs, (uint32_t)kBwdBatch) : 0u) * kStep;
+            const uint16_t* list = s_list[w * kStrips + strip];
+            auto walk = [&](auto checked) {
+                constexpr bool CHECK = decltype(checked)::value;
+                for (uint32_t i0 = 0; i0 < n_list; i0 += kBwdPad) {
+                    const uint32_t at2 = *reinterpret_cast<const uint32_t*>(list + i0);
 #pragma unroll
-            for (int q = 0; q < kG; ++q) comb[q * kBwdBatch + lane] = acc[q];
-        }
-        __syncthreads();
-        if ((uint32_t)tid < cnt) {
-            // the pair's slot is its emission position: a primitive's pairs end up
-            // side by side, for k_project_bwd to read contiguously
-            float v[kSlot] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-            if (work) {
-                const float* c0 = &s_row[0][0][0][0];
-                const float* c1 = &s_row[1][0][0][0];
-                const float* c2 = &s_row[2][0][0][0];
-                const float* c3 = &s_row[3][0][0][0];
-#pragma unroll
-                for (int q = 0; q < kG; ++q) {
-                    const int i = q * kBwdBatch + tid;
-                    v[q] = (c0[i] + c1[i]) + (c2[i] + c3[i]);
+                    for (int i = 0; i < kBwdPad; ++i) {
+                        const uint32_t at = i ? at2 >> 16 : at2 & 0xFFFFu;
+                        const Splat& S = *reinterpret_cast<const Splat*>(reinterpret_cast<const char*>(L) + 2 * at);
+                        const float u = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(s_u) + at / kSums);
+                        const float sigma = P.eval(S);
+                        const float gv = S.o * exp_neg(sigma);
+                        float al = CHECK ? fminf(kAlphaMax, gv) : gv;
+                        // a lane without the pair takes alpha = 0: its T stays, its weight and ds are 0
+                        bool ok = (at < last_b) & !(al < kAlphaMin);
+                        if (CHECK) ok = ok & !(sigma < kSigmaNeg);
+                        al = ok ? al : 0.0f;
+                        const float inv_om = __builtin_amdgcn_rcpf(1.0f - al);
+                        T = T * inv_om;
+                        const float gcol = gC0 * S.r + gC1 * S.g + gC2 * S.b;
+                        const float dalpha = gS * inv_om - T * gcol;        // -dL/dalpha
+                        const float wgt = al * T;
+                        gS = fmaf(wgt, gcol, gS);
+                        // the 0.99 cap stops d/d(opacity, sigma)
+                        const float ds = dalpha * (!CHECK || gv < kAlphaMax ? al : 0.0f);
+                        const float dx = u - xj;
+                        const float dsx = ds * dx;
+                        *reinterpret_cast<float*>(my_sums + at) =
+                            row_sum8(ds, dsx * dx, dsx, ds * h, dsx * h, wgt * gC1, wgt * gC0, wgt * gC2, odd);
+                    }
                 }
+            };
+            if (s_special)
+                walk(std::true_type{});
+            else
+                walk(std::false_type{});
+            __syncthreads();
+            // four threads per pair, two strips' rows of the tile each (both quadrants
+            // beside each other share the rows); the slot is the pair's emission
+            // position: a primitive's pairs end up side by side for k_slot_sum
+            const uint32_t k = (uint32_t)tid >> 2, part = (uint32_t)tid & 3u;
+            if (k < cnt) {
+                float acc[kG] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+                const float v = s_v[k];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const uint32_t row = 2u * part + i;                          // strip of the tile, downwards
+                    const uint32_t sl = (row >> 2) * 2u * kStrips + (row & 3u);  // in the left quadrant; the right one follows
+                    const float4 a0 = *reinterpret_cast<const float4*>(&s_sum[sl][k][0]);
+                    const float4 a1 = *reinterpret_cast<const float4*>(&s_sum[sl][k][4]);
+                    const float4 b0 = *reinterpret_cast<const float4*>(&s_sum[sl + kStrips][k][0]);
+                    const float4 b1 = *reinterpret_cast<const float4*>(&s_sum[sl + kStrips][k][4]);
+                    // as stored: a, c, b, d = m, m_x, m_xx, m_h; e, g, f, h = m_xh, colours
+                    const float sm = a0.x + b0.x, sx = a0.y + b0.y, sxx = a0.z + b0.z, sh = a0.w + b0.w,
+                                sxh = a1.x + b1.x;
+                    const float c = v - (2.0f * (float)row - 7.0f);
+                    const float my = fmaf(c, sm, -sh);
+                    acc[0] += sx;
+                    acc[1] += my;
+                    acc[2] += sxx;
+                    acc[3] += fmaf(c, sx, -sxh);
+                    acc[4] += fmaf(c, my - sh, 0.25f * sm);
+                    acc[5] += sm;
+                    acc[6] += a1.y + b1.y;
+                    acc[7] += a1.z + b1.z;
+                    acc[8] += a1.w + b1.w;
+                }
+#pragma unroll
+                for (int q = 0; q < kG; ++q) acc[q] = quad_add(acc[q]);
+                const float4 out = part == 0u   ? make_float4(acc[0], acc[1], acc[2], acc[3])
+                                   : part == 1u ? make_float4(acc[4], acc[5], acc[6], acc[7])
+                                                : make_float4(acc[8], 0.0f, 0.0f, 0.0f);
+                if (part < 3u) reinterpret_cast<float4*>(slots + (size_t)s_emit[k] * kSlot)[part] = out;
             }
-            float4* dst = reinterpret_cast<float4*>(slots + (size_t)pair_emit[start + bs + tid] * kSlot);
-            dst[0] = make_float4(v[0], v[1], v[2], v[3]);
-            dst[1] = make_float4(v[4], v[5], v[6], v[7]);
-            dst[2] = make_float4(v[8], v[9], v[10], v[11]);
+            __syncthreads();
         }
-        __syncthreads();
     }
 }
 
