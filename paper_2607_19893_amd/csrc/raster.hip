@@ -19,6 +19,7 @@
 // k_slot_sum adds its slots in order -- deterministic, no floating-point atomics
 // in global memory -- and k_project_bwd applies the projection and colour chain
 // rule (geometry in fp64) and writes one compact gradient row.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -915,11 +916,6 @@ __device__ __forceinline__ void geometry_bwd(const float* mu_f, const float* ls_
     out[9] = (float)((gz - z * along) * iq);
 }
 
-// Lists of up to kSerialSlots slots are summed by their own thread; longer
-// ones (a primitive spanning many tiles) by the whole wave, 256 slots a
-// round.  Either way the order is fixed, so the result is deterministic.
-constexpr uint32_t kSerialSlots = 8;
-
 template <int N>
 __device__ __forceinline__ void load_row(const float* __restrict__ src, float* dst) {
     if constexpr (N % 4 == 0) {
@@ -945,90 +941,154 @@ __device__ __forceinline__ uint32_t find_row(const uint32_t* __restrict__ u, uin
     return (lo < m && u[lo] == id) ? lo : m;
 }
 
+// A primitive's slots are added by 8 lanes: one slot per lane first, then four more
+// per lane; a primitive with more goes to a whole wave.
+constexpr uint32_t kOctSlots = 8, kOctSlots2 = 5 * kOctSlots;
+// Visible rows up to which 8 lanes take 4 primitives instead of 8, so that twice the
+// workgroups share them and one round of loads does.
+constexpr uint32_t kFewRows = 1u << 17;
+
+// The value of lane I of each 8 lanes, in all of them.
+template <int I>
+__device__ __forceinline__ uint32_t oct_bcast(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (I << 5) | 0x18);
+}
+
+// The sum over each 8 lanes, in all of them.
+__device__ __forceinline__ float oct_sum(float v) {
+    v = quad_add(v);
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, true));
+}
+
+__device__ __forceinline__ void add_slot(float (&a)[kG], const float4& x, const float4& y, float z) {
+    a[0] += x.x; a[1] += x.y; a[2] += x.z; a[3] += x.w;
+    a[4] += y.x; a[5] += y.y; a[6] += y.z; a[7] += y.w;
+    a[8] += z;
+}
+
 // Per visible row r: the sum of the primitive's pair slots (emission
 // positions pair_offset[id] .. + tiles[id], side by side; none if the pair
 // list overflowed its capacity), as one kSlot-float row at sums + kSlot r.
 // A kernel of its own: the chain rule's registers would leave the slot
 // stream too few waves to keep its loads in flight.
+//
+// Latency bounds it, so the lists are spread over lanes: each 8 lanes take 8 (or 4)
+// consecutive primitives, whose slots share cache lines, four at a time, with one
+// lane per slot and every load of the four in flight; longer lists get one round of
+// four slots per lane more, and the rare ones beyond that are left in LDS for the
+// workgroup's waves, 256 slots a round.  Every order is fixed, so the sums do not
+// depend on scheduling.  A thread per primitive with lists of more than 8 slots taken
+// whole by the wave one after the other, before, and this: 200k ring at 720p (6 slots
+// a primitive on average) 51 -> 18 us, 1M room 58 -> 37, 3M walk-through (2 slots)
+// 27 -> 23, 10k box 6.5 -> 4.8.
 __global__ void __launch_bounds__(GS_BLOCK) k_slot_sum(const uint32_t* __restrict__ vis_idx,
                                                        const uint32_t* __restrict__ vis_count,
                                                        const uint32_t* __restrict__ tiles,
                                                        const uint32_t* __restrict__ pair_offset,
                                                        const float* __restrict__ slots, uint32_t capacity,
                                                        float* __restrict__ sums) {
+    __shared__ uint3 s_long[GS_BLOCK];      // row, first slot and count of each list left for the waves
+    __shared__ uint32_t s_n;
     const uint32_t V = *vis_count;
-    // Rows in chunks of 16 consecutive ones (neighbouring rows' slots share
-    // cache lines); workgroup b takes chunks b, b + NB, b + 2 NB, ... (NB the
-    // workgroups needed), so a wave's four chunks lie across the whole list.
-    // In a spatially ordered pool the long slot lists of neighbours near the
-    // camera come in runs; taken whole by one wave they would be summed one
-    // after the other while the rest of the chip idles.
-    const uint32_t nb = (V + GS_BLOCK - 1) / GS_BLOCK;
+    // Workgroup b takes chunks b, b + NB, b + 2 NB, ... of consecutive rows (NB the
+    // workgroups needed): in a spatially ordered pool the long slot lists of
+    // neighbours near the camera come in runs, which one workgroup would
+    // otherwise add one after the other while the rest of the chip idles.
+    const uint32_t per = V <= kFewRows ? 4u : 8u;
+    const uint32_t per_block = GS_BLOCK / kOctSlots * per;
+    const uint32_t nb = (V + per_block - 1u) / per_block;
     if (blockIdx.x >= nb) return;
-    const uint32_t r = ((threadIdx.x >> 4) * nb + blockIdx.x) * 16u + (threadIdx.x & 15u);
-    const bool valid = r < V;
-    const uint32_t id = valid ? vis_idx[r] : 0u;
-    float g2[kG] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-    const uint32_t first = valid ? pair_offset[id] : 0u;
-    const uint32_t nt = valid ? tiles[id] : 0u;
-    const bool fits = (uint64_t)first + nt <= capacity;
-    if (fits && nt <= kSerialSlots) {
-        // up to four slots per round, all loads in flight
-        for (uint32_t k = 0; k < nt; k += 4) {
-            float4 v[4][3];
+    if (threadIdx.x == 0) s_n = 0u;
+    __syncthreads();
+    const uint32_t lane = lane_id(), at = lane & 7u;
+    const uint32_t r0 = ((threadIdx.x >> 3) * nb + blockIdx.x) * per;
+    // lane i of 8: the chunk's primitive i
+    const bool valid = at < per && r0 + at < V;
+    const uint32_t id = valid ? vis_idx[r0 + at] : 0u;
+    uint32_t first = valid ? pair_offset[id] : 0u;
+    uint32_t nt = valid ? tiles[id] : 0u;
+    if (!((uint64_t)first + nt <= capacity)) first = nt = 0u;
+    const bool is_long = nt > kOctSlots2;
+    if (is_long) {
+        s_long[atomicAdd(&s_n, 1u)] = make_uint3(r0 + at, first, nt);
+        first = nt = 0u;
+    }
+    const uint64_t longs = __ballot(is_long);
+    auto four = [&](auto i4) {
+        constexpr int I = decltype(i4)::value * 4;
+        const uint32_t f[4] = {oct_bcast<I>(first), oct_bcast<I + 1>(first), oct_bcast<I + 2>(first),
+                               oct_bcast<I + 3>(first)};
+        const uint32_t c[4] = {oct_bcast<I>(nt), oct_bcast<I + 1>(nt), oct_bcast<I + 2>(nt), oct_bcast<I + 3>(nt)};
+        float4 v[4][2];
+        float v8[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t q = first + min(k + j, nt - 1u);     // past the list: the last slot again, unused
-                const float4* sl = reinterpret_cast<const float4*>(slots + (size_t)q * kSlot);
-                v[j][0] = sl[0]; v[j][1] = sl[1]; v[j][2] = sl[2];
-            }
+        for (int u = 0; u < 4; ++u) {
+            const float4* sl = reinterpret_cast<const float4*>(
+                slots + (size_t)(f[u] + min(at, c[u] > 0u ? c[u] - 1u : 0u)) * kSlot);   // past the list: its last slot, unused
+            v[u][0] = sl[0];
+            v[u][1] = sl[1];
+            v8[u] = sl[2].x;
+        }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (k + j < nt) {
-                    g2[0] += v[j][0].x; g2[1] += v[j][0].y; g2[2] += v[j][0].z; g2[3] += v[j][0].w;
-                    g2[4] += v[j][1].x; g2[5] += v[j][1].y; g2[6] += v[j][1].z; g2[7] += v[j][1].w;
-                    g2[8] += v[j][2].x;
+        for (int u = 0; u < 4; ++u) {
+            float a[kG] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+            if (at < c[u]) add_slot(a, v[u][0], v[u][1], v8[u]);
+            if (__ballot(c[u] > kOctSlots) != 0ull) {
+                float4 x[4][2];
+                float x8[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const float4* sl = reinterpret_cast<const float4*>(
+                        slots + (size_t)(f[u] + min(at + kOctSlots * (k + 1), c[u] > 0u ? c[u] - 1u : 0u)) * kSlot);
+                    x[k][0] = sl[0];
+                    x[k][1] = sl[1];
+                    x8[k] = sl[2].x;
                 }
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (at + kOctSlots * (k + 1) < c[u]) add_slot(a, x[k][0], x[k][1], x8[k]);
             }
+#pragma unroll
+            for (int q = 0; q < kG; ++q) a[q] = oct_sum(a[q]);
+            const uint32_t r = r0 + I + u;
+            const bool left = ((longs >> ((lane & 56u) + I + u)) & 1ull) != 0ull;
+            if (at < 3u && r < V && !left)
+                reinterpret_cast<float4*>(sums + (size_t)r * kSlot)[at] =
+                    at == 0u   ? make_float4(a[0], a[1], a[2], a[3])
+                    : at == 1u ? make_float4(a[4], a[5], a[6], a[7])
+                               : make_float4(a[8], 0.0f, 0.0f, 0.0f);
+        }
+    };
+    four(std::integral_constant<int, 0>{});
+    if (per == 8u) four(std::integral_constant<int, 1>{});
+    __syncthreads();
+    for (uint32_t l = threadIdx.x / GS_WAVE; l < s_n; l += GS_BLOCK / GS_WAVE) {
+        const uint3 e = s_long[l];
+        float a[kG] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+        for (uint32_t k0 = 0; k0 < e.z; k0 += 4 * GS_WAVE) {
+            float4 x[4][2];
+            float x8[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float4* sl = reinterpret_cast<const float4*>(
+                    slots + (size_t)(e.y + min(k0 + j * GS_WAVE + lane, e.z - 1u)) * kSlot);
+                x[j][0] = sl[0];
+                x[j][1] = sl[1];
+                x8[j] = sl[2].x;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (k0 + j * GS_WAVE + lane < e.z) add_slot(a, x[j][0], x[j][1], x8[j]);
+        }
+#pragma unroll
+        for (int q = 0; q < kG; ++q) a[q] = wave_sum(a[q]);
+        if (lane == 0) {
+            float4* dst = reinterpret_cast<float4*>(sums + (size_t)e.x * kSlot);
+            dst[0] = make_float4(a[0], a[1], a[2], a[3]);
+            dst[1] = make_float4(a[4], a[5], a[6], a[7]);
+            dst[2] = make_float4(a[8], 0.0f, 0.0f, 0.0f);
         }
     }
-    // longer lists: the whole wave, 4 x 64 slots per round with coalesced loads,
-    // the lanes' partial sums added in a fixed order
-    uint64_t big = __ballot(fits && nt > kSerialSlots);
-    while (big) {
-        const int owner = __ffsll((unsigned long long)big) - 1;
-        big &= big - 1;
-        const uint32_t f = (uint32_t)__builtin_amdgcn_readlane((int)first, owner);
-        const uint32_t nb2 = (uint32_t)__builtin_amdgcn_readlane((int)nt, owner);
-        float acc[kG] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-        for (uint32_t k0 = 0; k0 < nb2; k0 += 4 * GS_WAVE) {
-            float4 v[4][3];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t k = min(k0 + j * GS_WAVE + lane_id(), nb2 - 1u);
-                const float4* sl = reinterpret_cast<const float4*>(slots + (size_t)(f + k) * kSlot);
-                v[j][0] = sl[0]; v[j][1] = sl[1]; v[j][2] = sl[2];
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (k0 + j * GS_WAVE + lane_id() < nb2) {
-                    acc[0] += v[j][0].x; acc[1] += v[j][0].y; acc[2] += v[j][0].z; acc[3] += v[j][0].w;
-                    acc[4] += v[j][1].x; acc[5] += v[j][1].y; acc[6] += v[j][1].z; acc[7] += v[j][1].w;
-                    acc[8] += v[j][2].x;
-                }
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < kG; ++q) {
-            const float sv = wave_sum(acc[q]);
-            if (lane_id() == owner) g2[q] = sv;
-        }
-    }
-    if (!valid) return;
-    float4* dst = reinterpret_cast<float4*>(sums + (size_t)r * kSlot);
-    dst[0] = make_float4(g2[0], g2[1], g2[2], g2[3]);
-    dst[1] = make_float4(g2[4], g2[5], g2[6], g2[7]);
-    dst[2] = make_float4(g2[8], 0.0f, 0.0f, 0.0f);
 }
 
 // Per visible row r: the primitive's 2D gradient (from its slot sums, row r
@@ -1269,7 +1329,9 @@ hipError_t launch_raster_bwd(const gs_scene& scene, const CamArgs& cam, const gs
     if (e != hipSuccess || scene.n == 0 || !(stages & 2)) return e;
     const dim3 grid(div_up(scene.n, GS_BLOCK));
     float* sums = slots + align256(sizeof(float) * kSlot * (size_t)(capacity > 0 ? capacity : 1)) / sizeof(float);
-    hipLaunchKernelGGL(k_slot_sum, grid, dim3(GS_BLOCK), 0, st, vis_idx, vis_count, proj.tiles, pair_offset, slots,
+    // the kernel decides on the visible rows, known on the device only: workgroups for either split
+    const dim3 sum_grid(std::max(grid.x, div_up(std::min((uint32_t)scene.n, kFewRows), GS_BLOCK / 2)));
+    hipLaunchKernelGGL(k_slot_sum, sum_grid, dim3(GS_BLOCK), 0, st, vis_idx, vis_count, proj.tiles, pair_offset, slots,
                        capacity, sums);
     if (union_idx) {
         if (first) {
