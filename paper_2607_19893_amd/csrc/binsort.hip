@@ -16,8 +16,8 @@
 //      its range depends on scheduling;
 //   4. each tile's segment is sorted by (depth bits, emission position), tiles
 //      taken in the dispatch order by a persistent grid: a wave sorts a tile of
-//      fewer than 512 pairs in registers, a workgroup one of up to 2048 (each
-//      wave 512 in registers, merges across waves through LDS), two exact runs
+//      fewer than 512 pairs in registers (256 where the tiles are few), a workgroup
+//      one of up to 2048 (its waves in registers, merges across waves through LDS), two exact runs
 //      in LDS merged by rank up to 4096, and a network in global memory beyond.
 //      The key is unique per pair, so the result does not depend on the order
 //      step 3 left; emission positions grow with the primitive id inside a
@@ -35,7 +35,7 @@ namespace gsmi {
 namespace {
 
 // Tile counters per LDS histogram pass of the emission and placement blocks
-// (32 KB); images with more tiles take several passes over the block's keys.
+// (32 KB); a block whose pairs span more tiles takes several passes over its keys.
 constexpr uint32_t kTileChunk = 8192;
 
 // Lanes of a wave whose digit equals this lane's digit (a 64-lane match built
@@ -129,14 +129,14 @@ __global__ void __launch_bounds__(GS_BLOCK) k_offsets(
 // The pairs [base, hi) of one emission block: pair i belongs to the last of
 // the block's nr ranks whose offset is <= i (a zero-tile rank shares its
 // successor's offset and is passed over; the offset after the range is taken
-// as +inf).  STAGED: offsets, ids and rectangles are read from the block's LDS
+// as +inf).  STAGED: offsets, ids, depths and rectangles are read from the block's LDS
 // copy, else from global memory (g_off, g_order: the range's first rank).
 // Per pair: tile (pkeys), primitive (pvals) and the primitive's depth bits
 // (pdepth); the tile of each of the thread's pairs is also left in key[]
 // (0xFFFFFFFF past hi).
 template <bool STAGED>
 __device__ __forceinline__ void emit_block_pairs(uint32_t base, uint32_t hi, uint32_t nr, const uint32_t* s_off,
-                                                 const uint32_t* s_gid, const ushort4* s_rect,
+                                                 const uint32_t* s_gid, const uint32_t* s_dep, const ushort4* s_rect,
                                                  const uint32_t* __restrict__ g_off,
                                                  const uint32_t* __restrict__ g_order,
                                                  const ushort4* __restrict__ rect, int32_t tiles_x,
@@ -162,14 +162,58 @@ __device__ __forceinline__ void emit_block_pairs(uint32_t base, uint32_t hi, uin
         key[k] = ty * (uint32_t)tiles_x + tx;
         pkeys[i] = key[k];
         pvals[i] = gid;
-        pdepth[i] = __float_as_uint(depth[gid]);
+        pdepth[i] = STAGED ? s_dep[lo] : __float_as_uint(depth[gid]);
     }
+}
+
+// Tiles up to which a block clears and reads the counters of all of them instead of
+// finding the range its pairs span.  The range costs about 1 us in each of the two
+// kernels (2170 tiles, pool in given order: emission and placement 31 us, with it 33)
+// and saves passes over counters that stay 0 (32,400 tiles: 112 -> 78 us; 8160: 46 -> 44).
+constexpr uint32_t kAllTiles = 4096;
+
+// First and last tile of the block's keys (0xFFFFFFFF: no pair; a block holds at
+// least one), within [0, T); all T tiles if there are few.  s: two words per wave.
+// Every thread of the block must call it: it ends with a barrier.
+__device__ __forceinline__ void block_key_range(const uint32_t (&key)[GS_ITEMS], uint32_t T, uint32_t* s, uint32_t* lo,
+                                                uint32_t* up) {
+    constexpr int kWaves = GS_BLOCK / GS_WAVE;
+    if (T <= kAllTiles) {
+        *lo = 0u;
+        *up = T - 1u;
+        __syncthreads();
+        return;
+    }
+    uint32_t a = 0xFFFFFFFFu, b = 0u;
+#pragma unroll
+    for (int k = 0; k < GS_ITEMS; ++k) {
+        a = min(a, key[k]);
+        b = max(b, key[k] == 0xFFFFFFFFu ? 0u : key[k]);
+    }
+#pragma unroll
+    for (int d = GS_WAVE / 2; d >= 1; d >>= 1) {
+        a = min(a, (uint32_t)__shfl_xor((int)a, d, GS_WAVE));
+        b = max(b, (uint32_t)__shfl_xor((int)b, d, GS_WAVE));
+    }
+    if (lane_id() == 0) {
+        s[threadIdx.x / GS_WAVE] = a;
+        s[kWaves + threadIdx.x / GS_WAVE] = b;
+    }
+    __syncthreads();
+    *lo = min(min(s[0], s[1]), min(s[2], s[3]));
+    *up = min(max(max(s[kWaves], s[kWaves + 1]), max(s[kWaves + 2], s[kWaves + 3])), T - 1u);
+}
+
+// Clears the nc counters of h (16-byte aligned).
+__device__ __forceinline__ void clear_counts(uint32_t* h, uint32_t nc) {
+    uint4* h4 = reinterpret_cast<uint4*>(h);
+    for (uint32_t d = threadIdx.x; d < (nc + 3u) / 4u; d += GS_BLOCK) h4[d] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 // One thread per pair: pair i belongs to the rank r with offs_r[r] <= i <
 // offs_r[r+1] and covers tile number i - offs_r[r] of that primitive's
 // rectangle (row-major).  Each block locates its rank range once, stages the
-// offsets, ids and rectangles of those ranks in LDS and binary-searches
+// offsets, ids, depths and rectangles of those ranks in LDS and binary-searches
 // there; key (tile id) and value (primitive id) stores are contiguous.  Then
 // the block counts its pairs per tile in LDS (the staging memory reused) and
 // adds every non-zero count to the tile's total.
@@ -179,34 +223,28 @@ __global__ void __launch_bounds__(GS_BLOCK) k_emit_pairs(
     const uint32_t* __restrict__ sort_count, int32_t tiles_x, uint32_t T, uint32_t* __restrict__ pkeys,
     uint32_t* __restrict__ pvals, uint32_t* __restrict__ pdepth, uint32_t* __restrict__ tcount) {
     constexpr uint32_t kStage = GS_TILE_ITEMS + 1;
-    static_assert(kStage * 16 >= kTileChunk * 4, "the tile histogram fits in the staging memory");
-    __shared__ __align__(16) unsigned char s_mem[kStage * 16];
+    static_assert(kStage * 20 >= kTileChunk * 4, "the tile histogram fits in the staging memory");
+    __shared__ __align__(16) unsigned char s_mem[(kStage * 20 + 15) / 16 * 16];
     ushort4* s_rect = reinterpret_cast<ushort4*>(s_mem);
     uint32_t* s_off = reinterpret_cast<uint32_t*>(s_mem + kStage * 8);
     uint32_t* s_gid = reinterpret_cast<uint32_t*>(s_mem + kStage * 12);
-    __shared__ uint32_t s_range[2];
+    uint32_t* s_dep = reinterpret_cast<uint32_t*>(s_mem + kStage * 16);
+    __shared__ uint32_t s_key[2 * GS_BLOCK / GS_WAVE];
     const uint32_t M = *sort_count;
     const uint32_t base = blockIdx.x * GS_TILE_ITEMS;
     if (base >= M) return;
     const uint32_t hi = min(base + (uint32_t)GS_TILE_ITEMS, M);
-    if (threadIdx.x == 0) {
-        // the ranks of the block's first and last pairs: the first from the table
-        // k_offsets wrote; the last is the next block's first rank, or the one
-        // before it when that rank starts exactly at hi (the last rank for the
-        // last block), stepping back over ranks that start later
-        const uint32_t r0 = bstart[blockIdx.x];
-        uint32_t r1 = hi == M ? *vis_count - 1u : bstart[blockIdx.x + 1];
-        while (r1 > r0 && offs_r[r1] > hi - 1u) --r1;
-        s_range[0] = r0;
-        s_range[1] = r1;
-    }
-    __syncthreads();
-    const uint32_t r0 = s_range[0];
-    // Ranks holding pairs of this block: at most GS_TILE_ITEMS + 1 when every
-    // rank holds >= 1 pair (the visible set of gs_project's tile counts); a
-    // caller list with zero-tile ids can span more, and then the block
-    // searches the offsets in global memory instead of staging them.
-    const uint32_t nr = s_range[1] - r0 + 1;
+    // The ranks of the block's first and last pairs: the first from the table
+    // k_offsets wrote; the next block's first rank bounds the last (it may start at
+    // hi or share its offset with ranks without pairs: then no pair of the block
+    // finds them), the last rank of all for the last block.
+    // They are at most GS_TILE_ITEMS + 1 when every rank holds >= 1 pair (the visible
+    // set of gs_project's tile counts); a caller list with zero-tile ids can span
+    // more, and then the block searches the offsets in global memory instead of
+    // staging them.
+    const uint32_t r0 = bstart[blockIdx.x];
+    const uint32_t r1 = hi == M ? *vis_count - 1u : bstart[blockIdx.x + 1];
+    const uint32_t nr = r1 - r0 + 1;
     const bool staged = nr <= kStage;
     if (staged) {
         for (uint32_t j = threadIdx.x; j < nr; j += GS_BLOCK) {
@@ -214,21 +252,25 @@ __global__ void __launch_bounds__(GS_BLOCK) k_emit_pairs(
             s_off[j] = offs_r[r0 + j];
             s_gid[j] = g;
             s_rect[j] = rect[g];
+            s_dep[j] = __float_as_uint(depth[g]);
         }
     }
     __syncthreads();
     uint32_t key[GS_ITEMS];
     if (staged)
-        emit_block_pairs<true>(base, hi, nr, s_off, s_gid, s_rect, offs_r + r0, order + r0, rect, tiles_x, depth,
+        emit_block_pairs<true>(base, hi, nr, s_off, s_gid, s_dep, s_rect, offs_r + r0, order + r0, rect, tiles_x, depth,
                                pkeys, pvals, pdepth, key);
     else
-        emit_block_pairs<false>(base, hi, nr, s_off, s_gid, s_rect, offs_r + r0, order + r0, rect, tiles_x, depth,
+        emit_block_pairs<false>(base, hi, nr, s_off, s_gid, s_dep, s_rect, offs_r + r0, order + r0, rect, tiles_x, depth,
                                 pkeys, pvals, pdepth, key);
+    // counts per tile, over the tiles from the block's first to its last: in a
+    // spatially ordered pool a block's pairs span a few rows of tiles
     uint32_t* h = reinterpret_cast<uint32_t*>(s_mem);
-    for (uint32_t c0 = 0; c0 < T; c0 += kTileChunk) {
-        const uint32_t nc = min(kTileChunk, T - c0);
-        __syncthreads();    // the staging (first chunk) or the last chunk's flush is done
-        for (uint32_t d = threadIdx.x; d < nc; d += GS_BLOCK) h[d] = 0u;
+    uint32_t lo, up;
+    block_key_range(key, T, s_key, &lo, &up);     // (the staging memory is free behind its barrier)
+    for (uint32_t c0 = lo; c0 <= up; c0 += kTileChunk) {
+        const uint32_t nc = min(kTileChunk, up - c0 + 1u);
+        clear_counts(h, nc);
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < GS_ITEMS; ++k)
@@ -238,6 +280,7 @@ __global__ void __launch_bounds__(GS_BLOCK) k_emit_pairs(
             const uint32_t c = h[d];
             if (c) atomicAdd(&tcount[c0 + d], c);
         }
+        __syncthreads();    // before the next chunk clears the counters
     }
 }
 
@@ -256,10 +299,15 @@ __device__ __forceinline__ uint32_t tile_order_key(uint32_t n) {
 
 // Tiles with fewer pairs than this are depth-sorted by one wave in registers;
 // the order key is monotone in the count, so these are exactly the tiles with
-// keys above kLongKey, and the dispatch order puts all others first.
-constexpr uint32_t kWaveSortMax = 512;
-constexpr uint32_t kLongKey = 255u - 96u;   // tile_order_key(512): code 16 * (9 - 3) + 0
-static_assert(kWaveSortMax == 512u, "kLongKey is the key of 512 pairs");
+// keys above long_key, and the dispatch order puts all others first.  Where the tiles
+// leave most of the chip idle (FEW, at most two per compute unit) a tile's own time
+// counts: its waves share it from 256 pairs on, with as few keys a lane as hold it
+// (256 tiles with one of 598 pairs: 15.8 -> 11.7 us, 475 tiles 17.4 -> 11.8).  With
+// more tiles the longer code and the barriers cost more (8160 tiles: 30 -> 35 us).
+template <bool FEW>
+constexpr uint32_t kWaveSortMax = FEW ? 256u : 512u;
+template <bool FEW>
+constexpr uint32_t kLongKey = FEW ? 255u - 80u : 255u - 96u;   // tile_order_key: code 16 * (8 - 3), 16 * (9 - 3)
 
 // Exclusive scan over the 4 waves of a workgroup of GS_BLOCK threads is
 // block_excl_scan.
@@ -274,7 +322,7 @@ constexpr int kFinishLoads = 32;
 // [0, 0) for a tile without pairs), the placement cursors (each range's
 // start), the dispatch order (tiles by ascending tile_order_key, equal keys
 // by ascending id) with one record per dispatch position (tile, range start,
-// pair count), and the number of tiles with kWaveSortMax pairs or more, which
+// pair count), and the number of tiles with keys up to long_key, which
 // the order puts first.  Workgroup b owns the tiles [b*kFinishSeg, ..) of one
 // segment.  It reads every total (all loads of a pass in flight together):
 // their sum before the segment starts its ranges, and the key counts over all
@@ -288,7 +336,7 @@ __global__ void __launch_bounds__(GS_BLOCK) k_tile_finish(const uint32_t* __rest
                                                           uint32_t* __restrict__ ranges,
                                                           uint32_t* __restrict__ cursor,
                                                           uint32_t* __restrict__ order, uint4* __restrict__ rec,
-                                                          uint32_t* __restrict__ n_long) {
+                                                          uint32_t long_key, uint32_t* __restrict__ n_long) {
     constexpr int kWaves = GS_BLOCK / GS_WAVE;
     __shared__ uint32_t s_all[256], s_before[256];
     __shared__ uint32_t s_wc[kWaves][256];
@@ -353,7 +401,7 @@ __global__ void __launch_bounds__(GS_BLOCK) k_tile_finish(const uint32_t* __rest
     {
         uint32_t ktot;
         const uint32_t kstart = block_excl_scan(s_all[tid], scratch, &ktot);
-        if (blockIdx.x == 0 && tid == kLongKey + 1u) *n_long = kstart;   // tiles with key <= kLongKey come first
+        if (blockIdx.x == 0 && tid == long_key + 1u) *n_long = kstart;   // tiles with key <= long_key come first
         s_all[tid] = kstart + s_before[tid];
     }
     // per wave: key counts of its quarter of the segment (its lanes' tiles, in order)
@@ -409,7 +457,8 @@ __global__ void __launch_bounds__(GS_BLOCK) k_tile_scatter(const uint32_t* __res
                                                            uint32_t* __restrict__ cursor,
                                                            unsigned long long* __restrict__ skey,
                                                            uint32_t* __restrict__ sval) {
-    __shared__ uint32_t h[kTileChunk];
+    __shared__ __align__(16) uint32_t h[kTileChunk];
+    __shared__ uint32_t s_key[2 * GS_BLOCK / GS_WAVE];
     const uint32_t M = *sort_count;
     const uint32_t base = blockIdx.x * GS_TILE_ITEMS + threadIdx.x;
     if (blockIdx.x * GS_TILE_ITEMS >= M) return;
@@ -422,9 +471,11 @@ __global__ void __launch_bounds__(GS_BLOCK) k_tile_scatter(const uint32_t* __res
         gid[k] = i < M ? pvals[i] : 0u;
         rk[k] = 0u;
     }
-    for (uint32_t c0 = 0; c0 < T; c0 += kTileChunk) {
-        const uint32_t nc = min(kTileChunk, T - c0);
-        for (uint32_t d = threadIdx.x; d < nc; d += GS_BLOCK) h[d] = 0u;
+    uint32_t lo, up;
+    block_key_range(key, T, s_key, &lo, &up);
+    for (uint32_t c0 = lo; c0 <= up; c0 += kTileChunk) {
+        const uint32_t nc = min(kTileChunk, up - c0 + 1u);
+        clear_counts(h, nc);
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < GS_ITEMS; ++k)
@@ -738,13 +789,13 @@ __device__ __forceinline__ void wave_sort_tile(uint32_t t, uint32_t start, uint3
     wave_sync();
 }
 
-// Long tiles: kWaveSortMax .. kLongCap pairs are sorted by the workgroup's
-// waves in registers, kWaveSortMax keys each; merges wider than one wave take
+// Long tiles: kWaveSortMax<FEW> .. kLongCap pairs are sorted by the workgroup's
+// waves in registers, 8 keys a lane (FEW: 2, 4 or 8); merges wider than one wave take
 // their cross-wave steps through LDS.  Longer tiles take the exact network in
 // global memory.
 constexpr int kSortWaves = GS_BLOCK / GS_WAVE;
-constexpr uint32_t kLongCap = kSortWaves * kWaveSortMax;
-constexpr int kLongK = (int)kWaveSortMax / GS_WAVE;     // keys per lane
+constexpr int kLongK = 8;                                // most keys per lane
+constexpr uint32_t kLongCap = GS_BLOCK * kLongK;
 // Workgroups per compute unit of the persistent depth-sort grid.
 constexpr uint32_t kDepthSortBlocksPerCU = 8;
 
@@ -890,44 +941,47 @@ __device__ void sort_huge_tile(uint32_t t, uint32_t start, uint32_t n, unsigned 
 }
 
 // One cross-wave step of a long tile: element i (register r of lane l of
-// wave w, i = w * 512 + l * 8 + r) against element i ^ mask.  Key and slot
-// go through LDS as one word pair, r-major (address r * 256 + i / 8), so the
+// wave w, i = (w * 64 + l) * K + r) against element i ^ mask.  Key and slot
+// go through LDS as one word pair, r-major (address r * 256 + i / K), so the
 // lanes of one access touch consecutive words.
-__device__ __forceinline__ void long_exchange(uint32_t (&v)[kLongK], uint32_t (&p)[kLongK], bool act, uint32_t ibase,
+template <int K>
+__device__ __forceinline__ void long_exchange(uint32_t (&v)[K], uint32_t (&p)[K], bool act, uint32_t ibase,
                                               uint32_t mask, unsigned long long* s_kv) {
-    constexpr uint32_t kStride = kLongCap / kLongK;
+    constexpr uint32_t kStride = GS_BLOCK;
     const uint32_t hb = 1u << (31 - __clz(mask));          // the highest bit of mask decides the side
     if (act) {
 #pragma unroll
-        for (int r = 0; r < kLongK; ++r) s_kv[r * kStride + (ibase >> 3)] = ((unsigned long long)p[r] << 32) | v[r];
+        for (int r = 0; r < K; ++r) s_kv[r * kStride + (ibase / K)] = ((unsigned long long)p[r] << 32) | v[r];
     }
     __syncthreads();
     if (act) {
-        const bool lower = (ibase & hb) == 0;              // hb >= 512 > r: one side for all r
+        const bool lower = (ibase & hb) == 0;              // hb >= 64 K > r: one side for all r
 #pragma unroll
-        for (int r = 0; r < kLongK; ++r) {
+        for (int r = 0; r < K; ++r) {
             const uint32_t q = (ibase + r) ^ mask;
-            const unsigned long long kv = s_kv[(q & 7u) * kStride + (q >> 3)];
+            const unsigned long long kv = s_kv[(q % K) * kStride + q / K];
             keep32(v[r], p[r], (uint32_t)kv, (uint32_t)(kv >> 32), lower);
         }
     }
     __syncthreads();
 }
 
-// A long tile (n in [kWaveSortMax, kLongCap]) by the whole workgroup.
-__device__ void sort_long_tile(uint32_t t, uint32_t start, uint32_t n, unsigned long long* __restrict__ skey,
+// A long tile (at most 256 K pairs) by the whole workgroup, K keys a lane.
+template <int K>
+__device__ __forceinline__ void sort_long_tile(uint32_t t, uint32_t start, uint32_t n, unsigned long long* __restrict__ skey,
                                uint32_t* __restrict__ sval, unsigned long long* s_kv, uint32_t* s_v,
                                uint32_t* s_first, uint32_t* __restrict__ pair_emit, uint32_t* __restrict__ vals,
                                uint64_t* __restrict__ keys64) {
     const uint32_t w = threadIdx.x / GS_WAVE, lane = lane_id();
-    uint32_t np = kWaveSortMax;
+    constexpr uint32_t kWave = GS_WAVE * K;      // keys of a wave
+    uint32_t np = kWave;
     while (np < n) np <<= 1;
-    const bool act = w < np / kWaveSortMax;
-    const uint32_t ibase = w * kWaveSortMax + lane * kLongK;
-    uint32_t v[kLongK], p[kLongK];
+    const bool act = w < np / kWave;
+    const uint32_t ibase = w * kWave + lane * K;
+    uint32_t v[K], p[K];
     bool odd = false;
 #pragma unroll
-    for (int r = 0; r < kLongK; ++r) {
+    for (int r = 0; r < K; ++r) {
         const uint32_t i = ibase + r;
         v[r] = act && i < n ? key_depth(skey, start + i) : kDepthPad;
         p[r] = i;
@@ -937,11 +991,11 @@ __device__ void sort_long_tile(uint32_t t, uint32_t start, uint32_t n, unsigned 
         block_sort_tile64(t, start, n, skey, sval, s_kv, s_v, pair_emit, vals, keys64);
         return;
     }
-    if (act) net32<kLongK, (int)kWaveSortMax>(v, p, lane);
-    for (uint32_t kk = 2 * kWaveSortMax; kk <= np; kk <<= 1) {
-        long_exchange(v, p, act, ibase, kk - 1, s_kv);
-        for (uint32_t j = kk >> 2; j >= kWaveSortMax; j >>= 1) long_exchange(v, p, act, ibase, j, s_kv);
-        if (act) tail32<kLongK, (int)kWaveSortMax / 2>(v, p, lane);
+    if (act) net32<K, (int)kWave>(v, p, lane);
+    for (uint32_t kk = 2 * kWave; kk <= np; kk <<= 1) {
+        long_exchange<K>(v, p, act, ibase, kk - 1, s_kv);
+        for (uint32_t j = kk >> 2; j >= kWave; j >>= 1) long_exchange<K>(v, p, act, ibase, j, s_kv);
+        if (act) tail32<K, (int)kWave / 2>(v, p, lane);
     }
     // equal neighbours: inside a lane, to the next lane, to the next wave
     if (act && lane == 0) s_first[w] = v[0];
@@ -949,17 +1003,17 @@ __device__ void sort_long_tile(uint32_t t, uint32_t start, uint32_t n, unsigned 
     bool tie = false;
     if (act) {
 #pragma unroll
-        for (int r = 0; r + 1 < kLongK; ++r) tie |= ibase + r + 1 < n && v[r] == v[r + 1];
+        for (int r = 0; r + 1 < K; ++r) tie |= ibase + r + 1 < n && v[r] == v[r + 1];
         const uint32_t next = __shfl_down(v[0], 1, GS_WAVE);
         if (lane + 1 < GS_WAVE)
-            tie |= ibase + kLongK < n && v[kLongK - 1] == next;
-        else if (w + 1 < np / kWaveSortMax)
-            tie |= ibase + kLongK < n && v[kLongK - 1] == s_first[w + 1];
+            tie |= ibase + K < n && v[K - 1] == next;
+        else if (w + 1 < np / kWave)
+            tie |= ibase + K < n && v[K - 1] == s_first[w + 1];
     }
     if (!__syncthreads_or(tie)) {
         if (act) {
 #pragma unroll
-            for (int r = 0; r < kLongK; ++r)
+            for (int r = 0; r < K; ++r)
                 if (ibase + r < n) put_by_slot(t, start, ibase + r, v[r], p[r], skey, sval, pair_emit, vals, keys64);
         }
         return;
@@ -967,7 +1021,7 @@ __device__ void sort_long_tile(uint32_t t, uint32_t start, uint32_t n, unsigned 
     // equal depth bits: the sorted keys to LDS, then each run placed by emission position
     if (act) {
 #pragma unroll
-        for (int r = 0; r < kLongK; ++r) {
+        for (int r = 0; r < K; ++r) {
             const uint32_t i = ibase + r;
             if (i < n) {
                 s_kv[i] = ((unsigned long long)v[r] << 32) | key_emit(skey, start + p[r]);
@@ -985,11 +1039,12 @@ __device__ void sort_long_tile(uint32_t t, uint32_t start, uint32_t n, unsigned 
 }
 
 // Per-tile depth sort, a persistent grid over the dispatch records.  The
-// first n_long records (kWaveSortMax pairs or more) go to whole workgroups,
+// first n_long records (kWaveSortMax<FEW> pairs or more) go to whole workgroups,
 // records b, b + G, .. to workgroup b; then every wave takes the remaining
 // records from the shortest up, records T-1-s for s = 4b + w, 4b + w + 4G, ..
 // Output: the tiles' pairs ordered by (depth bits, emission position), with
 // the primitive ids, the sorted -> emission map and the optional 64-bit keys.
+template <bool FEW>
 __global__ void __launch_bounds__(GS_BLOCK) k_tile_depth_sort(const uint4* __restrict__ rec,
                                                               const uint32_t* __restrict__ n_long_ptr, uint32_t T,
                                                               unsigned long long* __restrict__ skey,
@@ -997,34 +1052,41 @@ __global__ void __launch_bounds__(GS_BLOCK) k_tile_depth_sort(const uint4* __res
                                                               uint32_t* __restrict__ pair_emit,
                                                               uint32_t* __restrict__ vals,
                                                               uint64_t* __restrict__ keys64) {
-    __shared__ unsigned long long s_kv[kLongCap];      // long tiles; a 512-entry quarter per wave otherwise
+    __shared__ unsigned long long s_kv[kLongCap];      // long tiles; a quarter per wave otherwise
     __shared__ uint32_t s_v[kLongCap];
     __shared__ uint32_t s_first[kSortWaves];
     const uint32_t G = gridDim.x;                             // <= T
     const uint32_t w = threadIdx.x / GS_WAVE;
-    const uint32_t s0 = blockIdx.x * kSortWaves + w;
-    // the first records of the block and of the wave load beside the count
+    // the first record of the block loads beside the count
     uint4 rl = rec[blockIdx.x];
-    uint4 rs = rec[T - 1u - min(s0, T - 1u)];
     const uint32_t n_long = *n_long_ptr;
+    // the short tiles are dealt out, longest first, from the workgroups on that hold
+    // no long tile (or the fewest): those with one get the shortest tiles, or none
+    const uint32_t turn = n_long % G;
+    const uint32_t s0 = (blockIdx.x >= turn ? blockIdx.x - turn : blockIdx.x + G - turn) * kSortWaves + w;
+    uint4 rs = rec[min(n_long + s0, T - 1u)];
     for (uint32_t pos = blockIdx.x; pos < n_long; pos += G) {
         if (pos != blockIdx.x) rl = rec[pos];
-        if (rl.z <= kLongCap)
-            sort_long_tile(rl.x, rl.y, rl.z, skey, sval, s_kv, s_v, s_first, pair_emit, vals, keys64);
+        if (FEW && rl.z <= 2u * GS_BLOCK)
+            sort_long_tile<2>(rl.x, rl.y, rl.z, skey, sval, s_kv, s_v, s_first, pair_emit, vals, keys64);
+        else if (FEW && rl.z <= 4u * GS_BLOCK)
+            sort_long_tile<4>(rl.x, rl.y, rl.z, skey, sval, s_kv, s_v, s_first, pair_emit, vals, keys64);
+        else if (rl.z <= kLongCap)
+            sort_long_tile<8>(rl.x, rl.y, rl.z, skey, sval, s_kv, s_v, s_first, pair_emit, vals, keys64);
         else
             sort_huge_tile(rl.x, rl.y, rl.z, skey, sval, s_kv, s_v, pair_emit, vals, keys64);
     }
-    unsigned long long* sk = s_kv + w * kWaveSortMax;
-    uint32_t* sv = s_v + w * kWaveSortMax;
+    unsigned long long* sk = s_kv + w * (kLongCap / kSortWaves);
+    uint32_t* sv = s_v + w * (kLongCap / kSortWaves);
     for (uint32_t s = s0; s < T - n_long; s += kSortWaves * G) {
-        if (s != s0) rs = rec[T - 1u - s];
+        if (s != s0) rs = rec[n_long + s];
         const uint32_t t = rs.x, start = rs.y, n = rs.z;
-        if (n == 0u || n >= kWaveSortMax) continue;     // (the order puts every longer tile first)
+        if (n == 0u || n >= kWaveSortMax<FEW>) continue;     // (the order puts every longer tile first)
         if (n <= 64u)
             wave_sort_tile<1>(t, start, n, skey, sval, sk, sv, pair_emit, vals, keys64);
         else if (n <= 128u)
             wave_sort_tile<2>(t, start, n, skey, sval, sk, sv, pair_emit, vals, keys64);
-        else if (n <= 256u)
+        else if (FEW || n <= 256u)
             wave_sort_tile<4>(t, start, n, skey, sval, sk, sv, pair_emit, vals, keys64);
         else
             wave_sort_tile<8>(t, start, n, skey, sval, sk, sv, pair_emit, vals, keys64);
@@ -1090,10 +1152,12 @@ hipError_t launch_binsort(const gs_proj& proj, int32_t n, const uint32_t* vis_id
     uint32_t* tcount = at<uint32_t>(ws, L.tcount);
     uint32_t* cursor = at<uint32_t>(ws, L.cursor);
     uint32_t* order = tile_order ? tile_order : at<uint32_t>(ws, L.order);
+    const uint32_t cus = compute_units() ? compute_units() : 256u;
+    const bool few = T <= 2u * cus;
     // ranges, cursors and the dispatch order from the per-tile totals
     auto finish = [&]() {
         hipLaunchKernelGGL(k_tile_finish, dim3(div_up(T, kFinishSeg)), dim3(GS_BLOCK), 0, st, tcount, T, ranges,
-                           cursor, order, at<uint4>(ws, L.rec), ctr + 2);
+                           cursor, order, at<uint4>(ws, L.rec), few ? kLongKey<true> : kLongKey<false>, ctr + 2);
         return hipGetLastError();
     };
     // no pairs: empty ranges, and the order (then the tile ids)
@@ -1133,10 +1197,13 @@ hipError_t launch_binsort(const gs_proj& proj, int32_t n, const uint32_t* vis_id
     hipLaunchKernelGGL(k_tile_scatter, dim3(nbp), dim3(GS_BLOCK), 0, st, at<uint32_t>(ws, L.pkeys),
                        at<uint32_t>(ws, L.emit_id), at<uint32_t>(ws, L.pdepth), ctr + 1, T, cursor, skey, sval);
     // 5. per tile, longest first: depth order, primitive ids (+ optional 64-bit keys)
-    const uint32_t cus = compute_units();
-    const uint32_t grid = std::min<uint32_t>(T, (cus ? cus : 256u) * kDepthSortBlocksPerCU);
-    hipLaunchKernelGGL(k_tile_depth_sort, dim3(grid), dim3(GS_BLOCK), 0, st, at<uint4>(ws, L.rec), ctr + 2, T, skey,
-                       sval, pair_emit, vals, keys);
+    const dim3 grid(std::min<uint32_t>(T, cus * kDepthSortBlocksPerCU));
+    if (few)
+        hipLaunchKernelGGL(k_tile_depth_sort<true>, grid, dim3(GS_BLOCK), 0, st, at<uint4>(ws, L.rec), ctr + 2, T, skey,
+                           sval, pair_emit, vals, keys);
+    else
+        hipLaunchKernelGGL(k_tile_depth_sort<false>, grid, dim3(GS_BLOCK), 0, st, at<uint4>(ws, L.rec), ctr + 2, T, skey,
+                           sval, pair_emit, vals, keys);
     return hipGetLastError();
 }
 

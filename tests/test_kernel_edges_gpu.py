@@ -1,0 +1,257 @@
+"""Edges of the kernels' size classes and dispatch rules, with inputs made for
+them: per-tile sort sizes on few and on many tiles, footprints that only a caller's
+own arrays can hold (indefinite conics, opacities above the cap), slot lists of
+every length class, predicate bytes at odd sizes and addresses."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_gpu():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need an MI355X"
+    return torch
+
+
+@pytest.fixture(scope="module")
+def gs():
+    from paper_2607_19893_amd import gsmi
+    return gsmi
+
+
+def host_u32(t, k=None):
+    a = t.detach().cpu().numpy().view(np.uint32).reshape(-1)
+    return a if k is None else a[:k]
+
+
+SORT_SIZES = [1, 63, 64, 65, 128, 129, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025, 2047, 2048, 2049]
+
+
+# 256 tiles (at most two per compute unit), 1200 (more), 7500 (a block's counters cover
+# the range of its own tiles) and 37,500 (several passes over them)
+@pytest.mark.parametrize("width,height", [(256, 256), (640, 480), (1600, 1200), (4000, 2400)])
+def test_bin_sort_sizes(width, height, torch_gpu, gs):
+    torch = torch_gpu
+    rng = np.random.default_rng(width)
+    TX, TY = (width + 15) // 16, (height + 15) // 16
+    T = TX * TY
+    tile = np.concatenate([np.full(k, t) for t, k in zip(rng.choice(T, len(SORT_SIZES), replace=False), SORT_SIZES)] +
+                          [rng.integers(0, T, 3000)]).astype(np.int64)
+    rng.shuffle(tile)
+    n = tile.size
+    # a primitive covers its tile, every seventh two beside each other
+    x0, y0 = tile % TX, tile // TX
+    wide = (np.arange(n) % 7 == 0) & (x0 + 1 < TX)
+    rect = np.stack([x0, y0, x0 + 1 + wide, y0 + 1], 1).astype(np.int16)
+    depth = rng.uniform(1.0, 9.0, n).astype(np.float32)
+    depth[rng.choice(n, n // 10, replace=False)] = np.float32(2.5)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    u32 = lambda k: torch.zeros(max(1, k), dtype=torch.int32, device="cuda")  # noqa: E731
+    f = lambda *s: torch.zeros(*s, device="cuda")  # noqa: E731
+    keep = dict(radius=u32(n), tiles=dev((1 + wide).astype(np.int32)), rect=dev(rect), depth=dev(depth), mean2d=f(n, 2),
+                conic_opacity=f(n, 4), rgb=f(n, 3), clamp=torch.zeros(n, dtype=torch.uint8, device="cuda"))
+    proj = gs.make_proj(**keep)
+    M = int((1 + wide).sum())
+    cap = M + 5
+    vals, emit, ranges, order, off = u32(cap), u32(cap), u32(2 * T), u32(T), u32(n)
+    cnt, status = u32(2), u32(4)
+    ws = torch.zeros(gs.gs_workspace_bytes(gs.GS_WS_BIN_SORT, n, cap, width, height), dtype=torch.uint8, device="cuda")
+    gs.gs_bin_sort(proj, n, dev(np.arange(n, dtype=np.int32)), dev(np.array([n], np.int32)), width, height, cap, vals,
+                   ranges, off, emit, None, cnt[:1], status, ws, tile_order=order)
+    torch.cuda.synchronize()
+    assert host_u32(status)[0] == 0 and host_u32(cnt)[0] == M
+    ids = np.concatenate([np.arange(n), np.flatnonzero(wide)])
+    tiles = np.concatenate([tile, tile[wide] + 1])
+    ref = np.lexsort((ids, depth[ids].view(np.uint32), tiles))
+    np.testing.assert_array_equal(host_u32(vals, M), ids[ref])
+    count = np.bincount(tiles, minlength=T)
+    start = np.cumsum(count) - count
+    np.testing.assert_array_equal(host_u32(ranges).reshape(T, 2)[count > 0], np.stack([start, start + count], 1)[count > 0])
+    # each sorted pair names the emission position of its (primitive, tile)
+    first = np.cumsum(1 + wide) - (1 + wide)
+    np.testing.assert_array_equal(host_u32(emit, M), (first[ids] + (tiles != tile[ids]))[ref])
+
+
+def reference(u, con, op, rgb, order, W, H, dL):
+    """Image, final T, and the gradients of (u, v, A, B, C, opacity, rgb) in 64 bits, every
+    pixel blending all pairs in order; with each pixel's distance to its nearest decision."""
+    import torch
+    q = torch.tensor(np.concatenate([u, con, op[:, None], rgb], 1)[order], dtype=torch.float64, requires_grad=True)
+    ys, xs = np.mgrid[0:H, 0:W]
+    px = torch.tensor(xs.reshape(-1) + 0.5, dtype=torch.float64)[:, None]
+    py = torch.tensor(ys.reshape(-1) + 0.5, dtype=torch.float64)[:, None]
+    dx, dy = q[:, 0] - px, q[:, 1] - py
+    sig = 0.5 * (q[:, 2] * dx * dx + q[:, 4] * dy * dy) + q[:, 3] * dx * dy
+    raw = q[:, 5] * torch.exp(-sig)
+    al = torch.clamp(raw, max=float(np.float32(0.99)))
+    with torch.no_grad():
+        ok = (sig >= 0) & (al >= float(np.float32(1 / 255)))
+        T = torch.cumprod(1 - al * ok, 1)
+        take = ok & (T >= float(np.float32(1e-4)))
+        near = torch.minimum((al * 255 - 1).abs().amin(1), torch.where(ok, (T / 1e-4 - 1).abs(), 1.0).amin(1))
+        near = torch.minimum(near, (raw / 0.99 - 1).abs().amin(1))
+        near = torch.minimum(near, torch.where(raw.detach() * 255 > 0.9, sig.abs() * 1e3 + (sig == 0), 1.0).amin(1))
+    al = al * take
+    Tk = torch.cumprod(torch.cat([torch.ones(al.shape[0], 1, dtype=torch.float64), 1 - al[:, :-1]], 1), 1)
+    img = ((al * Tk)[:, :, None] * q[:, 6:9]).sum(1)
+    (img * torch.tensor(dL.reshape(3, -1).T.astype(np.float64))).sum().backward()
+    g = np.zeros((len(order), 9))
+    g[order] = q.grad.numpy()
+    last = np.where(take.any(1), take.shape[1] - torch.flip(take, [1]).int().argmax(1).numpy(), 0)
+    return img.detach().numpy().T.reshape(3, H, W), (Tk[:, -1] * (1 - al[:, -1])).detach().numpy().reshape(H, W), g, \
+        near.numpy().reshape(H, W), last.reshape(H, W)
+
+
+# one pair; the edges of a backward batch (64) and of a forward batch (256), several batches
+@pytest.mark.parametrize("n,width,height", [(1, 16, 16), (64, 37, 29), (65, 37, 29), (257, 24, 41), (700, 21, 18)])
+def test_raster_special_pairs(n, width, height, torch_gpu):
+    """Every pair in every tile's list, among them indefinite conics, opacities above the
+    0.99 cap and below 1/255, and thin footprints centred far outside the image."""
+    from paper_2607_19893_amd import scenes
+    from paper_2607_19893_amd.pipeline import ViewTrainer
+    torch = torch_gpu
+    rng = np.random.default_rng(1000 + n)
+    sc = scenes.tiny(n=n).scene
+    cam = scenes.look_at((0.0, 0.0, -4.0), (0.0, 0.0, 0.0), (0.0, -1.0, 0.0), width, height, 60.0)
+    tx, ty = (width + 15) // 16, (height + 15) // 16
+    tr = ViewTrainer(sc, capacity=n * tx * ty + 64, max_width=width, max_height=height, with_replica=False)
+    uv = rng.uniform(-6, 1, (n, 2)) + rng.random((n, 2)) * [width + 10, height + 10]
+    s1, s2 = np.exp(rng.uniform(-0.5, 2.5, n)), np.exp(rng.uniform(-0.5, 2.5, n))
+    th = rng.uniform(0, np.pi, n)
+    op = rng.uniform(0.02, 0.35, n)
+    kind = np.arange(n) % 11 if n > 1 else np.array([0])
+    op[kind == 3] = rng.uniform(0.991, 1.0, (kind == 3).sum())
+    op[kind == 5] = rng.uniform(0.0, 0.0039, (kind == 5).sum())
+    far = kind == 7                                     # thin, 150..300 px long, centred off the image
+    s1[far], s2[far] = rng.uniform(60, 120, far.sum()), 0.6
+    uv[far] += np.stack([np.cos(th[far]), np.sin(th[far])], 1) * rng.uniform(80, 150, far.sum())[:, None]
+    c, s = np.cos(th), np.sin(th)
+    A, B, C = (c / s1) ** 2 + (s / s2) ** 2, c * s * (s1 ** -2 - s2 ** -2), (s / s1) ** 2 + (c / s2) ** 2
+    bad = kind == 9                                     # indefinite: sigma < 0 in a double wedge
+    B[bad] = np.sqrt(A[bad] * C[bad]) * rng.uniform(1.05, 2.0, bad.sum())
+    u32f = lambda a: np.ascontiguousarray(a, np.float32)  # noqa: E731
+    uv, con, op = u32f(uv), u32f(np.stack([A, B, C], 1)), u32f(op)
+    rgb = u32f(rng.random((n, 3)))
+    depth = u32f(rng.permutation(n) + 1.0)
+    dL = u32f(rng.uniform(-1, 1, (3, height, width)))
+    order = np.argsort(depth)
+    img, fT, _, near, last = reference(uv, con, op, rgb, order, width, height, dL)
+    sure = near > 2e-5              # fp32 alpha and T of these few hundred pairs lie closer than that to the 64-bit ones
+    assert sure.mean() > 0.97
+    dL *= sure                      # an undecided pixel passes on no gradient
+    g = reference(uv, con, op, rgb, order, width, height, dL)[2]
+    tr.project(cam)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    tr.tiles.copy_(dev(np.full(n, tx * ty, np.int32)))
+    tr.rect.copy_(dev(np.tile(np.array([0, 0, tx, ty], np.int16), (n, 1))))
+    tr.depth.copy_(dev(depth))
+    tr.mean2d.copy_(dev(uv))
+    tr.conic.copy_(dev(np.concatenate([con, op[:, None]], 1)))
+    tr.rgb.copy_(dev(rgb))
+    tr.clamp.zero_()
+    tr.visible()
+    tr.bin_sort()
+    tr.raster_fwd(active=True)
+    tr.set_dL(dL)
+    tr.raster_bwd(grad2d=True)
+    torch.cuda.synchronize()
+    assert tr.host_status()[0] == 0
+    hw = width * height
+    got = tr.img.view(-1)[:3 * hw].cpu().numpy().reshape(3, height, width)
+    # T after k pairs carries 2k roundings of 2^-24: 700 pairs, 8.4e-5
+    assert np.abs(got - img)[:, sure].max() <= 1e-4
+    assert np.abs(tr.final_T.view(-1)[:hw].cpu().numpy().reshape(height, width) - fT)[sure].max() <= 1e-4
+    np.testing.assert_array_equal(host_u32(tr.n_contrib, hw).reshape(height, width)[sure], last[sure])
+    g2 = tr.grad2d.cpu().numpy()[:n].astype(np.float64)
+    # a term passes through T's 2n roundings forward and as many back; sums cancel to a
+    # column's rms at most
+    bound = (4 * n + 200) * 2.0 ** -24 * (np.abs(g) + np.sqrt((g ** 2).mean(0)))
+    assert (np.abs(g2 - g) <= bound + 1e-9).all(), np.abs((g2 - g) / (bound + 1e-12)).max(0)
+
+
+# lists of every length class of the slot sums, on few and on many visible rows
+@pytest.mark.parametrize("V", [5, 700, (1 << 17), (1 << 17) + 77])
+def test_slot_sums(V, torch_gpu):
+    from paper_2607_19893_amd import scenes
+    from paper_2607_19893_amd.pipeline import ViewTrainer
+    torch = torch_gpu
+    rng = np.random.default_rng(V)
+    nt = rng.integers(1, 5, V)
+    special = [1, 7, 8, 9, 39, 40, 41, 64, 255, 256, 257, 1000]
+    at = rng.choice(V, min(V, 5 * len(special)), replace=False)
+    nt[at] = np.resize(special, at.size)
+    M = int(nt.sum())
+    sc = scenes.tiny(n=V).scene
+    cam = scenes.tiny(n=10).cameras[0]
+    tr = ViewTrainer(sc, capacity=M, max_width=cam.width, max_height=cam.height, with_replica=False)
+    tr.project(cam)
+    off = np.cumsum(nt) - nt
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    tr.vis_idx.copy_(dev(np.arange(V, dtype=np.int32)))
+    tr.counts[0:1].copy_(dev(np.array([V], np.int32)))
+    tr.tiles.copy_(dev(nt.astype(np.int32)))
+    tr.pair_offset.copy_(dev(off.astype(np.int32)))
+    tr.conic.copy_(dev(np.tile(np.array([1, 0, 1, 1], np.float32), (V, 1))))
+    slots = rng.standard_normal((M, 12)).astype(np.float32)      # nine sums and padding per pair
+    tr.ws_bwd.view(torch.float32)[:M * 12].copy_(dev(slots.reshape(-1)))
+    tr.raster_bwd_project(grad2d=True)
+    torch.cuda.synchronize()
+    s = np.add.reduceat(slots[:, :9].astype(np.float64), off, 0)
+    mag = np.add.reduceat(np.abs(slots[:, :9]).astype(np.float64), off, 0)
+    scale = np.array([1, 1, 0.5, 1, 0.5, -1, 1, 1, 1])
+    err = np.abs(tr.grad2d.cpu().numpy()[:V] - s * scale)
+    # at most 4 + 8 + 6 additions in a row per value, each 2^-24 of the summed magnitudes
+    assert (err <= 20 * 2.0 ** -24 * mag * np.abs(scale) + 1e-12).all()
+
+
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 8191, 8193, 100003])
+@pytest.mark.parametrize("shift", [0, 1, 16])
+def test_scope_from_bytes(n, shift, torch_gpu, gs):
+    torch = torch_gpu
+    rng = np.random.default_rng(n + shift)
+    a = np.where(rng.random(n) < 0.3, rng.choice([1, 2, 127, 128, 255], n), 0).astype(np.uint8)
+    buf = torch.full((n + shift + 64,), 255, dtype=torch.uint8, device="cuda")
+    buf[shift:shift + n] = torch.from_numpy(a).cuda()
+    words = gs.scope_words(n)
+    sc = torch.full((words + 1,), -1, dtype=torch.int32, device="cuda")
+    gs.gs_scope_from_pred(gs.GS_PRED_U8_NONZERO, buf[shift:shift + n], n, 0, sc)
+    bits = np.zeros(words * 32, np.uint8)
+    bits[:n] = a != 0
+    ref = np.packbits(bits, bitorder="little").view(np.uint32)
+    np.testing.assert_array_equal(host_u32(sc, words), ref)
+    assert host_u32(sc)[words] == 0xFFFFFFFF
+    b = (rng.random(n) < 0.2).astype(np.uint8)
+    buf[shift:shift + n] = torch.from_numpy(b).cuda()
+    gs.gs_scope_from_pred(gs.GS_PRED_U8_NONZERO, buf[shift:shift + n], n, 1, sc)
+    bits[:n] |= b
+    np.testing.assert_array_equal(host_u32(sc, words), np.packbits(bits, bitorder="little").view(np.uint32))
+
+
+# 4096 blocks of 8192 ids are summed by the scatter itself, one more by a pass of its own
+@pytest.mark.parametrize("n", [4096 * 8192, 4096 * 8192 + 5])
+def test_hazard_lists_over_many_blocks(n, torch_gpu, gs):
+    torch = torch_gpu
+    rng = np.random.default_rng(3)
+    sets = [np.unique(np.concatenate([rng.integers(0, n, 20000), [0, n - 1]])) for _ in range(2)]
+    RA, WB = sets
+    WA = np.unique(np.concatenate([RA[::2], rng.integers(0, n, 500)]))
+    RB = np.unique(np.concatenate([WB, RA[::3], WA[::5]]))
+
+    def scope(ids):
+        w = np.zeros(gs.scope_words(n), np.uint32)
+        np.bitwise_or.at(w, ids >> 5, np.uint32(1) << (ids & 31).astype(np.uint32))
+        return torch.from_numpy(w.view(np.int32)).cuda()
+
+    s = [scope(x) for x in (RA, WA, RB, WB)]
+    out = [torch.zeros(gs.scope_words(n), dtype=torch.int32, device="cuda") for _ in range(3)]
+    ids = [torch.zeros(60000, dtype=torch.int32, device="cuda") for _ in range(3)]
+    counts = torch.zeros(4, dtype=torch.int32, device="cuda")
+    ws = torch.zeros(gs.gs_workspace_bytes(gs.GS_WS_SCOPE, n), dtype=torch.uint8, device="cuda")
+    gs.gs_scope_conflicts(*s, n, *out, *ids, counts, ws)
+    ref = [np.intersect1d(WB, WA), np.intersect1d(np.setdiff1d(RB, WB), WA),
+           np.setdiff1d(np.intersect1d(WB, RA), WA)]
+    np.testing.assert_array_equal(host_u32(counts), [r.size for r in ref] + [RB.size])
+    for t, r in zip(ids, ref):
+        np.testing.assert_array_equal(host_u32(t, r.size), r)
