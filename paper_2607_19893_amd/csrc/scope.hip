@@ -4,9 +4,9 @@
 //
 // Hazards, per bitmap word (one thread per word):
 //   WAW = W(B) & W(A),  RAW = R(B) & ~W(B) & W(A),  WAR = W(B) & R(A) & ~W(A)
-// Three launches: per-block popcounts, one workgroup that turns them into
-// per-block offsets and totals, and the scatter of ascending ids (skipped
-// when no id list is asked for).
+// Two launches: per-block popcounts, and the scatter of ascending ids, in which each
+// block adds up the counts before it (one workgroup turns them into offsets and
+// totals instead when no id list is asked for or the blocks are many).
 //
 // Admission, for the delayed set D = RAW: per-block partial counts
 // (|R(B)|, |D|, |C_A|, delayed ids without evidence, delayed ids whose
@@ -70,6 +70,32 @@ __global__ void __launch_bounds__(GS_BLOCK) k_scope_from_pred(const void* __rest
         const uint32_t v = lane == 0 ? (uint32_t)m : (uint32_t)(m >> 32);
         scope[w0 + lane] = accumulate ? (scope[w0 + lane] | v) : v;
     }
+}
+
+// The non-zero bytes of x as bits 0..3.
+__device__ __forceinline__ uint32_t byte_bits(uint32_t x) {
+    const uint32_t y = (((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x) >> 7 & 0x01010101u;
+    return (y | y >> 7 | y >> 14 | y >> 21) & 0xFu;
+}
+
+// The same for bytes at a 16-byte-aligned src, one word of the bitmap per thread: two
+// 16-byte loads of 32 bytes where a byte per lane left the memory system idle (3M ids:
+// 4.8 us -> 2.8 us).
+__global__ void __launch_bounds__(GS_BLOCK) k_scope_from_bytes(const uint8_t* __restrict__ src, int32_t n,
+                                                               int32_t accumulate, uint32_t* __restrict__ scope) {
+    const uint32_t w = blockIdx.x * GS_BLOCK + threadIdx.x;
+    const uint32_t nwords = ((uint32_t)n + 31u) >> 5;
+    if (w >= nwords) return;
+    uint32_t v = 0u;
+    if (32u * w + 32u <= (uint32_t)n) {
+        const uint4* s4 = reinterpret_cast<const uint4*>(src) + 2 * (size_t)w;
+        const uint4 a = s4[0], b = s4[1];
+        v = byte_bits(a.x) | byte_bits(a.y) << 4 | byte_bits(a.z) << 8 | byte_bits(a.w) << 12 | byte_bits(b.x) << 16 |
+            byte_bits(b.y) << 20 | byte_bits(b.z) << 24 | byte_bits(b.w) << 28;
+    } else {
+        for (uint32_t i = 32u * w; i < (uint32_t)n; ++i) v |= src[i] != 0u ? 1u << (i & 31u) : 0u;
+    }
+    scope[w] = accumulate ? (scope[w] | v) : v;
 }
 
 // ---------------------------------------------------------------------------
@@ -157,18 +183,70 @@ __device__ __forceinline__ void scatter_bits(uint32_t word, uint32_t base_id, ui
     }
 }
 
+// Blocks up to which the scatter adds up the counts of the blocks before it itself (a
+// few 16-byte loads a thread) instead of after k_hazard_offsets: the one-workgroup
+// launch took 5.6 us of 17 at 367 blocks.  Beyond, the loads (which grow with the
+// square of the blocks) outweigh it.
+constexpr uint32_t kSumBlocks = 4096;
+
+// SUM: partial holds the blocks' counts, and the last block writes the totals; else it
+// holds their offsets.
+template <bool SUM>
 __global__ void __launch_bounds__(GS_BLOCK) k_hazard_scatter(ScopeIn s, int32_t n, uint32_t nwords,
-                                                             const uint32_t* __restrict__ offsets,
+                                                             const uint32_t* __restrict__ partial,
                                                              uint32_t* __restrict__ waw_idx,
                                                              uint32_t* __restrict__ raw_idx,
-                                                             uint32_t* __restrict__ war_idx) {
+                                                             uint32_t* __restrict__ war_idx,
+                                                             uint32_t* __restrict__ counts) {
     __shared__ uint32_t scratch[4];
+    __shared__ uint4 s_before[GS_BLOCK / GS_WAVE];
+    const uint4* records = reinterpret_cast<const uint4*>(partial);
+    uint4 before;
+    if (SUM) {
+        uint4 acc = make_uint4(0u, 0u, 0u, 0u);
+        for (uint32_t i = threadIdx.x; i < blockIdx.x; i += 4 * GS_BLOCK) {
+            uint4 v[4];
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j)
+                v[j] = i + j * GS_BLOCK < blockIdx.x ? records[i + j * GS_BLOCK] : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                acc.x += v[j].x;
+                acc.y += v[j].y;
+                acc.z += v[j].z;
+                acc.w += v[j].w;
+            }
+        }
+        acc.x = wave_sum_u32(acc.x);
+        acc.y = wave_sum_u32(acc.y);
+        acc.z = wave_sum_u32(acc.z);
+        acc.w = wave_sum_u32(acc.w);
+        if (lane_id() == 0) s_before[threadIdx.x / GS_WAVE] = acc;
+        __syncthreads();
+        before = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+        for (int j = 0; j < GS_BLOCK / GS_WAVE; ++j) {
+            before.x += s_before[j].x;
+            before.y += s_before[j].y;
+            before.z += s_before[j].z;
+            before.w += s_before[j].w;
+        }
+        if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+            const uint4 own = records[blockIdx.x];
+            counts[0] = before.x + own.x;
+            counts[1] = before.y + own.y;
+            counts[2] = before.z + own.z;
+            counts[3] = before.w + own.w;
+        }
+    } else {
+        before = records[blockIdx.x];
+    }
     const uint32_t w = blockIdx.x * kWordsPerBlock + threadIdx.x;
     const Hazards h = hazard_words(s, w, nwords, n);
     uint32_t tot;
-    const uint32_t p0 = block_excl_scan(__popc(h.waw), scratch, &tot) + offsets[4 * blockIdx.x + 0];
-    const uint32_t p1 = block_excl_scan(__popc(h.raw), scratch, &tot) + offsets[4 * blockIdx.x + 1];
-    const uint32_t p2 = block_excl_scan(__popc(h.war), scratch, &tot) + offsets[4 * blockIdx.x + 2];
+    const uint32_t p0 = block_excl_scan(__popc(h.waw), scratch, &tot) + before.x;
+    const uint32_t p1 = block_excl_scan(__popc(h.raw), scratch, &tot) + before.y;
+    const uint32_t p2 = block_excl_scan(__popc(h.war), scratch, &tot) + before.z;
     const uint32_t base = w << 5;
     if (waw_idx) scatter_bits(h.waw, base, p0, waw_idx);
     if (raw_idx) scatter_bits(h.raw, base, p1, raw_idx);
@@ -208,107 +286,116 @@ __device__ __forceinline__ float wave_max_f32(float v) {
     return v;
 }
 
+// Words of a gate block: every wave loads all 64, one per lane, and takes a quarter of
+// the 32 passes over their 2048 ids.  The loads of a wave's passes are in flight
+// together (a wave with 32 passes of its own, four in flight: 12.4 us at 3M ids; this: 7.4 us).
+constexpr int kGateWords = GS_WAVE;
+constexpr int kGatePasses = kGateWords / 2 / (GS_BLOCK / GS_WAVE);
+
 __global__ void __launch_bounds__(GS_BLOCK) k_gate_partial(GateIn in, int32_t n, uint32_t nwords,
                                                            GatePartial* __restrict__ partial) {
-    __shared__ uint32_t scratch[4];
     __shared__ double s_sum[4];
     __shared__ float s_max[4];
-    const uint32_t w = blockIdx.x * kWordsPerBlock + threadIdx.x;
+    __shared__ uint32_t s_second[4];
+    const int lane = lane_id(), wv = threadIdx.x / GS_WAVE;
+    const uint32_t w0 = blockIdx.x * kGateWords, w = w0 + (uint32_t)lane;
     const uint32_t mask = tail_mask(w, nwords, n);
-    const uint32_t rb = load_word(in.RB, w, nwords, mask);
     const uint32_t d = load_word(in.D, w, nwords, mask);
     const uint32_t ca = load_word(in.CA, w, nwords, mask);
-    const uint32_t ev = load_word(in.E, w, nwords, mask);
-    uint32_t second = 0;
-    if (in.skip != nullptr) {
-        uint32_t x = d;
-        while (x) {
-            const int b = __ffs(x) - 1;
-            const uint32_t s = in.skip[(w << 5) + (uint32_t)b];
-            second += (s != 0u && s != in.version) ? 1u : 0u;
-            x &= x - 1u;
-        }
+    // pass j covers ids [64 j, 64 j + 64) of the block's, lane l taking id 64 j + l,
+    // whose bit sits in the word of lane 2 j + (l >> 5)
+    float gv[kGatePasses];
+    uint32_t sk[kGatePasses];
+    bool act[kGatePasses], del[kGatePasses];
+    const uint32_t bit = 1u << (lane & 31);
+#pragma unroll
+    for (int j = 0; j < kGatePasses; ++j) {
+        const int src = 2 * (wv * kGatePasses + j) + (lane >> 5);
+        act[j] = ((uint32_t)__shfl((int)ca, src, GS_WAVE) & bit) != 0u;
+        del[j] = ((uint32_t)__shfl((int)d, src, GS_WAVE) & bit) != 0u;
+        const uint32_t id = ((w0 + (uint32_t)src) << 5) + (uint32_t)(lane & 31);
+        gv[j] = act[j] || del[j] ? in.g[id] : 0.0f;
+        sk[j] = del[j] && in.skip != nullptr ? in.skip[id] : 0u;
     }
-    // ||g_A|| gathers: the wave's 64 words are 2048 consecutive ids; pass j
-    // covers ids [64 j, 64 j + 64) of them, lane l taking id 64 j + l, whose
-    // bit sits in the word of lane 2 j + (l >> 5).
-    const int lane = lane_id();
-    const uint32_t wave_w0 = w - (uint32_t)lane;
     double sum = 0.0;
     float mx = 0.0f;
-#pragma unroll 4
-    for (int j = 0; j < 32; ++j) {
-        const int src = 2 * j + (lane >> 5);
-        const uint32_t cw = (uint32_t)__shfl((int)ca, src, GS_WAVE);
-        const uint32_t dw = (uint32_t)__shfl((int)d, src, GS_WAVE);
-        const uint32_t bit = 1u << (lane & 31);
-        if ((cw | dw) & bit) {
-            const float gv = in.g[((wave_w0 + (uint32_t)src) << 5) + (uint32_t)(lane & 31)];
-            if (cw & bit) sum += (double)gv;
-            if (dw & bit) mx = fmaxf(mx, gv);
+    uint32_t second = 0;
+#pragma unroll
+    for (int j = 0; j < kGatePasses; ++j) {
+        if (act[j]) sum += (double)gv[j];
+        if (del[j]) mx = fmaxf(mx, gv[j]);
+        second += sk[j] != 0u && sk[j] != in.version ? 1u : 0u;
+    }
+    sum = wave_sum_f64(sum);
+    mx = wave_max_f32(mx);
+    second = wave_sum_u32(second);
+    if (lane == 0) {
+        s_sum[wv] = sum;
+        s_max[wv] = mx;
+        s_second[wv] = second;
+    }
+    __syncthreads();
+    if (wv != 0) return;
+    const uint32_t rb = load_word(in.RB, w, nwords, mask);
+    const uint32_t ev = load_word(in.E, w, nwords, mask);
+    GatePartial p;
+    p.n_read = wave_sum_u32(__popc(rb));
+    p.n_delayed = wave_sum_u32(__popc(d));
+    p.n_active = wave_sum_u32(__popc(ca));
+    p.n_missing = wave_sum_u32(__popc(d & ~ev));
+    p.n_second = (s_second[0] + s_second[1]) + (s_second[2] + s_second[3]);
+    p.max_bits = __float_as_uint(fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3])));
+    p.pad0 = p.pad1 = 0;
+    p.sum_g = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
+    p.pad2 = 0.0;
+    if (lane == 0) partial[blockIdx.x] = p;
+}
+
+// One workgroup: fixed-order reduction of the partials (four records a thread in
+// flight), then the decision.
+__global__ void __launch_bounds__(GS_BLOCK) k_gate_decide(const GatePartial* __restrict__ partial, uint32_t nb,
+                                                          double tau, gs_gate_result* __restrict__ out) {
+    constexpr int kWaves = GS_BLOCK / GS_WAVE, U = 4;
+    __shared__ double s_sum[kWaves];
+    __shared__ uint32_t s_cnt[5][kWaves];
+    __shared__ float s_max[kWaves];
+    uint32_t c[5] = {0u, 0u, 0u, 0u, 0u};
+    double sum = 0.0;
+    float mx = 0.0f;
+    for (uint32_t b = threadIdx.x; b < nb; b += U * GS_BLOCK) {
+        GatePartial p[U];
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) p[u] = partial[min(b + u * GS_BLOCK, nb - 1u)];
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            if (b + u * GS_BLOCK >= nb) continue;
+            c[0] += p[u].n_read;
+            c[1] += p[u].n_delayed;
+            c[2] += p[u].n_active;
+            c[3] += p[u].n_missing;
+            c[4] += p[u].n_second;
+            sum += p[u].sum_g;
+            mx = fmaxf(mx, __uint_as_float(p[u].max_bits));
         }
     }
     sum = wave_sum_f64(sum);
     mx = wave_max_f32(mx);
-    const int wv = threadIdx.x / GS_WAVE;
-    if (lane == 0) {
+#pragma unroll
+    for (int k = 0; k < 5; ++k) c[k] = wave_sum_u32(c[k]);
+    if (lane_id() == 0) {
+        const int wv = threadIdx.x / GS_WAVE;
         s_sum[wv] = sum;
         s_max[wv] = mx;
-    }
-    const uint32_t nR = block_sum_u32(__popc(rb), scratch);
-    const uint32_t nD = block_sum_u32(__popc(d), scratch);
-    const uint32_t nC = block_sum_u32(__popc(ca), scratch);
-    const uint32_t nM = block_sum_u32(__popc(d & ~ev), scratch);
-    const uint32_t nS = block_sum_u32(second, scratch);
-    if (threadIdx.x == 0) {
-        GatePartial p;
-        p.n_read = nR;
-        p.n_delayed = nD;
-        p.n_active = nC;
-        p.n_missing = nM;
-        p.n_second = nS;
-        p.max_bits = __float_as_uint(fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3])));
-        p.pad0 = p.pad1 = 0;
-        p.sum_g = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
-        p.pad2 = 0.0;
-        partial[blockIdx.x] = p;
-    }
-}
-
-// One workgroup: fixed-order reduction of the partials, then the decision.
-__global__ void __launch_bounds__(GS_BLOCK) k_gate_decide(const GatePartial* __restrict__ partial, uint32_t nb,
-                                                          double tau, gs_gate_result* __restrict__ out) {
-    __shared__ double s_sum[GS_BLOCK];
-    __shared__ uint32_t s_cnt[5][GS_BLOCK];
-    __shared__ float s_max[GS_BLOCK];
-    uint32_t c[5] = {0u, 0u, 0u, 0u, 0u};
-    double sum = 0.0;
-    float mx = 0.0f;
-    for (uint32_t b = threadIdx.x; b < nb; b += GS_BLOCK) {
-        const GatePartial p = partial[b];
-        c[0] += p.n_read;
-        c[1] += p.n_delayed;
-        c[2] += p.n_active;
-        c[3] += p.n_missing;
-        c[4] += p.n_second;
-        sum += p.sum_g;
-        mx = fmaxf(mx, __uint_as_float(p.max_bits));
-    }
-    s_sum[threadIdx.x] = sum;
-    s_max[threadIdx.x] = mx;
 #pragma unroll
-    for (int k = 0; k < 5; ++k) s_cnt[k][threadIdx.x] = c[k];
+        for (int k = 0; k < 5; ++k) s_cnt[k][wv] = c[k];
+    }
     __syncthreads();
-    for (int h = GS_BLOCK / 2; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) {
-            s_sum[threadIdx.x] += s_sum[threadIdx.x + h];
-            s_max[threadIdx.x] = fmaxf(s_max[threadIdx.x], s_max[threadIdx.x + h]);
-#pragma unroll
-            for (int k = 0; k < 5; ++k) s_cnt[k][threadIdx.x] += s_cnt[k][threadIdx.x + h];
-        }
-        __syncthreads();
-    }
     if (threadIdx.x != 0) return;
+    for (int k = 1; k < kWaves; ++k) {
+        s_sum[0] += s_sum[k];
+        s_max[0] = fmaxf(s_max[0], s_max[k]);
+        for (int q = 0; q < 5; ++q) s_cnt[q][0] += s_cnt[q][k];
+    }
     const uint32_t nR = s_cnt[0][0], nD = s_cnt[1][0], nC = s_cnt[2][0], nM = s_cnt[3][0], nS = s_cnt[4][0];
     const double rho = nR > 0 ? (double)nD / (double)nR : 0.0;
     const double mean = nC > 0 ? s_sum[0] / (double)nC : 0.0;
@@ -363,7 +450,8 @@ __global__ void __launch_bounds__(GS_BLOCK) k_gate_mark(const uint32_t* __restri
 }  // namespace
 
 size_t scope_ws_bytes(int32_t n) {
-    const uint32_t nb = div_up(div_up((uint64_t)(n > 0 ? n : 0), 32), kWordsPerBlock);
+    // the gate's records; the hazard counts (16 bytes per 256 words) are fewer
+    const uint32_t nb = div_up(div_up((uint64_t)(n > 0 ? n : 0), 32), kGateWords);
     return align256(sizeof(GatePartial) * (size_t)(nb + 1));
 }
 
@@ -385,6 +473,11 @@ hipError_t launch_scope_from_ids(const uint32_t* idx, const uint32_t* count, int
 hipError_t launch_scope_from_pred(int kind, const void* src, int32_t n, int32_t accumulate, uint32_t* scope,
                                   hipStream_t st) {
     if (n <= 0) return hipSuccess;
+    if (kind != GS_PRED_U32_NONZERO && (reinterpret_cast<uintptr_t>(src) & 15u) == 0u) {
+        hipLaunchKernelGGL(k_scope_from_bytes, dim3(div_up(div_up((uint64_t)n, 32), GS_BLOCK)), dim3(GS_BLOCK), 0, st,
+                           static_cast<const uint8_t*>(src), n, accumulate, scope);
+        return hipGetLastError();
+    }
     const dim3 grid(div_up((uint64_t)n, GS_BLOCK));
     if (kind == GS_PRED_U32_NONZERO)
         hipLaunchKernelGGL(k_scope_from_pred<GS_PRED_U32_NONZERO>, grid, dim3(GS_BLOCK), 0, st, src, n, accumulate,
@@ -406,18 +499,24 @@ hipError_t launch_scope_conflicts(const uint32_t* RA, const uint32_t* WA, const 
     hipLaunchKernelGGL(k_hazard_count, dim3(nb), dim3(GS_BLOCK), 0, st, s, n, nwords, waw, raw, war, partial);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    const bool lists = waw_idx || raw_idx || war_idx;
+    if (lists && nb <= kSumBlocks) {
+        hipLaunchKernelGGL(k_hazard_scatter<true>, dim3(nb), dim3(GS_BLOCK), 0, st, s, n, nwords, partial, waw_idx,
+                           raw_idx, war_idx, counts);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_hazard_offsets, dim3(1), dim3(GS_BLOCK), 0, st, partial, nb, counts);
     e = hipGetLastError();
-    if (e != hipSuccess || !(waw_idx || raw_idx || war_idx)) return e;
-    hipLaunchKernelGGL(k_hazard_scatter, dim3(nb), dim3(GS_BLOCK), 0, st, s, n, nwords, partial, waw_idx, raw_idx,
-                       war_idx);
+    if (e != hipSuccess || !lists) return e;
+    hipLaunchKernelGGL(k_hazard_scatter<false>, dim3(nb), dim3(GS_BLOCK), 0, st, s, n, nwords, partial, waw_idx,
+                       raw_idx, war_idx, counts);
     return hipGetLastError();
 }
 
 hipError_t launch_admission_gate(const uint32_t* RB, const uint32_t* D, const gs_gate_args& a, int32_t n,
                                  gs_gate_result* result, void* ws, hipStream_t st) {
     const uint32_t nwords = div_up((uint64_t)(n > 0 ? n : 0), 32);
-    const uint32_t nb = div_up(nwords, kWordsPerBlock);
+    const uint32_t nb = div_up(nwords, kGateWords);
     GatePartial* partial = static_cast<GatePartial*>(ws);
     const GateIn in{RB, D, a.active, a.evidence ? a.evidence : a.active, a.g, a.skip, a.producer_version};
     if (nb > 0) {
@@ -428,8 +527,8 @@ hipError_t launch_admission_gate(const uint32_t* RB, const uint32_t* D, const gs
     hipLaunchKernelGGL(k_gate_decide, dim3(1), dim3(GS_BLOCK), 0, st, partial, nb, a.tau, result);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.skip == nullptr || nb == 0) return e;
-    hipLaunchKernelGGL(k_gate_mark, dim3(nb), dim3(GS_BLOCK), 0, st, D, n, nwords, result, a.producer_version,
-                       a.skip);
+    hipLaunchKernelGGL(k_gate_mark, dim3(div_up(nwords, kWordsPerBlock)), dim3(GS_BLOCK), 0, st, D, n, nwords, result,
+                       a.producer_version, a.skip);
     return hipGetLastError();
 }
 
