@@ -108,9 +108,17 @@ __global__ void __launch_bounds__(GS_BLOCK) k_pack(GroupArgs a, const uint32_t* 
 }
 
 // Header and id check; sets GS_DEV_MSG_MISMATCH when the message cannot be applied.
+// RING (the commit of a slot): also the slot's version and the commit order, by one
+// thread of the same launch (a launch of its own took 3 us of a commit).
+template <bool RING>
 __global__ void __launch_bounds__(GS_BLOCK) k_apply_check(GroupArgs a, const uint32_t* __restrict__ msg,
                                                           uint64_t msg_capacity, int32_t n_rows, int32_t max_rows,
+                                                          uint32_t version, const uint32_t* __restrict__ ring_state,
                                                           gs_device_status* __restrict__ status) {
+    if (RING && blockIdx.x == 0 && threadIdx.x == 0) {
+        if (msg[2] != version) atomicOr(&status->flags, GS_DEV_MSG_MISMATCH);
+        else if (ring_state[0] + 1u != version) atomicOr(&status->flags, GS_DEV_MSG_ORDER);
+    }
     bool bad = false;
     const uint32_t K = msg[1];
     if (msg[0] != GS_MSG_MAGIC || msg[3] != (uint32_t)a.row_len || msg[4] != (uint32_t)a.n_groups ||
@@ -184,12 +192,6 @@ __global__ void __launch_bounds__(GS_BLOCK) k_apply(GroupArgs a, const uint32_t*
 // published version is older than the message's, each stamped with it, and
 // the skip markers that name this version cleared; finally the ring's
 // committed version and the counts of applied / left rows.
-__global__ void k_commit_order(const uint32_t* __restrict__ msg, uint32_t version,
-                               const uint32_t* __restrict__ ring_state, gs_device_status* __restrict__ status) {
-    if (msg[2] != version) atomicOr(&status->flags, GS_DEV_MSG_MISMATCH);
-    else if (ring_state[0] + 1u != version) atomicOr(&status->flags, GS_DEV_MSG_ORDER);
-}
-
 // UNI (rows of more than 32 floats, one row per wave): the row index and
 // its id are wave-uniform, so the id comes from a scalar load and stays in
 // scalar registers, which leaves room for the rows in flight.
@@ -312,9 +314,8 @@ hipError_t launch_publish_commit(const gs_ring& ring, uint32_t version, const gs
     const uint32_t* msg = static_cast<const uint32_t*>(ring.slot[version & 1u]);
     uint32_t cb = div_up((uint64_t)(max_rows > 0 ? max_rows : 1), GS_BLOCK);
     if (cb > 4096) cb = 4096;
-    hipLaunchKernelGGL(k_apply_check, dim3(cb), dim3(GS_BLOCK), 0, st, a, msg, (uint64_t)ring.slot_bytes, n_rows,
-                       max_rows, status);
-    hipLaunchKernelGGL(k_commit_order, dim3(1), dim3(1), 0, st, msg, version, ring.state, status);
+    hipLaunchKernelGGL(k_apply_check<true>, dim3(cb), dim3(GS_BLOCK), 0, st, a, msg, (uint64_t)ring.slot_bytes, n_rows,
+                       max_rows, version, ring.state, status);
     uint32_t blocks = row_blocks(max_rows, a.rows_per_wave * kRowsInFlight);
     if (ring.background) {
         const uint32_t cus = compute_units();
@@ -354,8 +355,8 @@ hipError_t launch_delta_apply(const void* msg, size_t msg_capacity, const gs_gro
     const GroupArgs a = make_group_args(dst, n_groups);
     uint32_t cb = div_up((uint64_t)(max_rows > 0 ? max_rows : 1), GS_BLOCK);
     if (cb > 4096) cb = 4096;
-    hipLaunchKernelGGL(k_apply_check, dim3(cb), dim3(GS_BLOCK), 0, st, a, static_cast<const uint32_t*>(msg),
-                       (uint64_t)msg_capacity, n_rows, max_rows, status);
+    hipLaunchKernelGGL(k_apply_check<false>, dim3(cb), dim3(GS_BLOCK), 0, st, a, static_cast<const uint32_t*>(msg),
+                       (uint64_t)msg_capacity, n_rows, max_rows, 0u, nullptr, status);
     const dim3 grid(row_blocks(max_rows, a.rows_per_wave * kRowsInFlight));
     if (a.rows_per_wave == 1)
         hipLaunchKernelGGL(k_apply<true>, grid, dim3(GS_BLOCK), 0, st, a, static_cast<const uint32_t*>(msg), mode,
