@@ -74,6 +74,53 @@ def test_bin_sort_sizes(width, height, torch_gpu, gs):
     np.testing.assert_array_equal(host_u32(emit, M), (first[ids] + (tiles != tile[ids]))[ref])
 
 
+# ids without tiles: none, every third, all but one in a hundred (a block of 2048 pairs
+# then spans more ranks than it has pairs)
+@pytest.mark.parametrize("empty", [0.0, 0.34, 0.99])
+def test_bin_sort_rectangles(empty, torch_gpu, gs):
+    """Rectangles of 1 to 6000 tiles, beginning and ending anywhere in a thread's eight
+    pairs and a block's 2048."""
+    torch = torch_gpu
+    width, height = 1600, 1216
+    TX, TY = 100, 76
+    T = TX * TY
+    rng = np.random.default_rng(int(empty * 100))
+    n = 60000 if empty > 0.9 else 3000
+    w, h = rng.integers(1, 6, n), rng.integers(1, 6, n)
+    big = rng.choice(n, n // 100, replace=False)
+    w[big], h[big] = rng.integers(1, TX + 1, big.size), rng.integers(1, 61, big.size)
+    w[big[0]], h[big[0]] = TX, 60
+    x0, y0 = rng.integers(0, TX - w + 1), rng.integers(0, TY - h + 1)
+    tiles = np.where(rng.uniform(size=n) < empty, 0, w * h)
+    tiles[big[0]] = TX * 60
+    rect = np.stack([x0, y0, x0 + w, y0 + h], 1).astype(np.int16)
+    depth = rng.uniform(1.0, 9.0, n).astype(np.float32)
+    listed = rng.permutation(n).astype(np.int32)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    u32 = lambda k: torch.zeros(max(1, k), dtype=torch.int32, device="cuda")  # noqa: E731
+    f = lambda *s: torch.zeros(*s, device="cuda")  # noqa: E731
+    keep = dict(radius=u32(n), tiles=dev(tiles.astype(np.int32)), rect=dev(rect), depth=dev(depth), mean2d=f(n, 2),
+                conic_opacity=f(n, 4), rgb=f(n, 3), clamp=torch.zeros(n, dtype=torch.uint8, device="cuda"))
+    M = int(tiles.sum())
+    cap = M + 7
+    vals, emit, ranges, order, off = u32(cap), u32(cap), u32(2 * T), u32(T), u32(n)
+    cnt, status = u32(2), u32(4)
+    ws = torch.zeros(gs.gs_workspace_bytes(gs.GS_WS_BIN_SORT, n, cap, width, height), dtype=torch.uint8, device="cuda")
+    gs.gs_bin_sort(gs.make_proj(**keep), n, dev(listed), dev(np.array([n], np.int32)), width, height, cap, vals, ranges,
+                   off, emit, None, cnt[:1], status, ws, tile_order=order)
+    torch.cuda.synchronize()
+    assert host_u32(status)[0] == 0 and host_u32(cnt)[0] == M
+    ids = np.repeat(listed, tiles[listed])
+    local = np.arange(M) - np.repeat(np.cumsum(tiles[listed]) - tiles[listed], tiles[listed])
+    tile = (y0[ids] + local // w[ids]) * TX + x0[ids] + local % w[ids]
+    ref = np.lexsort((ids, depth[ids].view(np.uint32), tile))
+    np.testing.assert_array_equal(host_u32(vals, M), ids[ref])
+    np.testing.assert_array_equal(host_u32(emit, M), ref)
+    count = np.bincount(tile, minlength=T)
+    start = np.cumsum(count) - count
+    np.testing.assert_array_equal(host_u32(ranges).reshape(T, 2)[count > 0], np.stack([start, start + count], 1)[count > 0])
+
+
 def reference(u, con, op, rgb, order, W, H, dL):
     """Image, final T, and the gradients of (u, v, A, B, C, opacity, rgb) in 64 bits, every
     pixel blending all pairs in order; with each pixel's distance to its nearest decision."""
