@@ -513,17 +513,37 @@ __global__ void __launch_bounds__(GS_BLOCK) k_tile_finish(const uint32_t* __rest
     }
 }
 
+// A pair's record: 12 bytes without padding (16 cost the sort 1 to 2 us a view in
+// cache misses).
+struct PairRec {
+    uint32_t emit, depth, gid;
+};
+static_assert(sizeof(PairRec) == 12, "three words a pair in the workspace");
+
+// The 64-bit key of a record, and a key in its place (the primitive stays).
+__device__ __forceinline__ unsigned long long rec_key(const PairRec& r) {
+    return ((unsigned long long)r.depth << 32) | r.emit;
+}
+__device__ __forceinline__ void put_key(PairRec* r, unsigned long long k) {
+    r->emit = (uint32_t)k;
+    r->depth = (uint32_t)(k >> 32);
+}
+
 // Placement of the emitted pairs in their tiles' ranges: the block ranks its
 // pairs per tile in LDS, claims one run of slots per distinct tile from the
-// tile's cursor, and writes each pair's depth-sort key at its slot (the depth
-// bits above the emission position) and the pair's primitive beside it.
+// tile's cursor, and writes each pair's record at its slot: the depth-sort key (the
+// depth bits above the emission position) and the primitive.  What bounds it are the
+// scattered stores, by their number more than their bytes: one of 12 bytes a pair in
+// place of 8 + 4 in two arrays.  Measured: 2.9M pairs at 3840x2160 51.7 -> 36.9 us (with
+// the sort that reads them 95.4 -> 80.3), a 1M-primitive room's view 25.0 -> 21.1 (53.3 ->
+// 50.8).  The key alone, with the primitive looked up by emission position, placed 4 us
+// faster still and cost the sort 17.
 __global__ void __launch_bounds__(GS_BLOCK) k_tile_scatter(const uint32_t* __restrict__ pkeys,
                                                            const uint32_t* __restrict__ pvals,
                                                            const uint32_t* __restrict__ pdepth,
                                                            const uint32_t* __restrict__ sort_count, uint32_t T,
                                                            uint32_t* __restrict__ cursor,
-                                                           unsigned long long* __restrict__ skey,
-                                                           uint32_t* __restrict__ sval) {
+                                                           PairRec* __restrict__ rec) {
     __shared__ __align__(16) uint32_t h[kTileChunk];
     __shared__ uint32_t s_key[2 * GS_BLOCK / GS_WAVE];
     const uint32_t M = *sort_count;
@@ -557,8 +577,7 @@ __global__ void __launch_bounds__(GS_BLOCK) k_tile_scatter(const uint32_t* __res
         for (int k = 0; k < GS_ITEMS; ++k)
             if (key[k] - c0 < nc) {
                 const uint32_t at = h[key[k] - c0] + rk[k];
-                skey[at] = ((unsigned long long)dep[k] << 32) | (base + k * GS_BLOCK);
-                sval[at] = gid[k];
+                rec[at] = PairRec{base + k * GS_BLOCK, dep[k], gid[k]};
             }
         __syncthreads();    // before the next chunk clears the counters
     }
@@ -583,8 +602,8 @@ constexpr uint32_t kRunMax = 64;
 // The exact network on a segment of global memory of any length n, by a
 // whole workgroup: entries at n and beyond are taken as kKeyMax, so a
 // compare-exchange that reaches past the data leaves the lower (real) entry
-// in place.  Payloads move with their keys.
-__device__ void bitonic_global(unsigned long long* s, uint32_t* pay, uint32_t n) {
+// in place.  Only the keys move.
+__device__ void bitonic_global(PairRec* s, uint32_t n) {
     uint32_t np = 1;
     while (np < n) np <<= 1;
     for (uint32_t k = 2; k <= np; k <<= 1) {
@@ -594,13 +613,10 @@ __device__ void bitonic_global(unsigned long long* s, uint32_t* pay, uint32_t n)
                 const uint32_t i = ((c & ~(j - 1)) << 1) | (c & (j - 1));
                 const uint32_t q = i ^ mask;
                 if (q >= n) continue;
-                const unsigned long long a = s[i], b = s[q];
+                const unsigned long long a = rec_key(s[i]), b = rec_key(s[q]);
                 if (b < a) {
-                    const uint32_t pa = pay[i], pb = pay[q];
-                    s[i] = b;
-                    s[q] = a;
-                    pay[i] = pb;
-                    pay[q] = pa;
+                    put_key(&s[i], b);
+                    put_key(&s[q], a);
                 }
             }
             __threadfence_block();
@@ -616,28 +632,27 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Writes sorted pair `at` of tile t: its emission position, primitive id and
-// optional 64-bit key.
-__device__ __forceinline__ void put_sorted(uint32_t t, uint32_t at, unsigned long long k, uint32_t gid,
-                                           uint32_t* __restrict__ pair_emit, uint32_t* __restrict__ vals,
+// Writes sorted pair `at` of tile t: its emission position, primitive id (pvals holds
+// them by emission position) and optional 64-bit key.
+__device__ __forceinline__ void put_sorted(uint32_t t, uint32_t at, unsigned long long k,
+                                           const uint32_t* __restrict__ pvals, uint32_t* __restrict__ pair_emit, uint32_t* __restrict__ vals,
                                            uint64_t* __restrict__ keys64) {
-    vals[at] = gid;
+    vals[at] = pvals[(uint32_t)k];
     pair_emit[at] = (uint32_t)k;
     if (keys64) keys64[at] = ((uint64_t)t << 32) | (k >> 32);
 }
 
 // The exact network over the n (<= 512) 64-bit keys of a tile by one wave,
-// in the wave's own LDS (sk, sv: 512 entries).
-__device__ void wave_sort_tile64(uint32_t t, uint32_t start, uint32_t n, const unsigned long long* __restrict__ skey,
-                                 const uint32_t* __restrict__ sval, unsigned long long* sk, uint32_t* sv,
+// in the wave's own LDS (sk: 512 entries).
+__device__ void wave_sort_tile64(uint32_t t, uint32_t start, uint32_t n, const PairRec* __restrict__ skey,
+                                 const uint32_t* __restrict__ pvals, unsigned long long* sk,
                                  uint32_t* __restrict__ pair_emit, uint32_t* __restrict__ vals,
                                  uint64_t* __restrict__ keys64) {
     const uint32_t lane = lane_id();
     uint32_t np = 2;
     while (np < n) np <<= 1;
     for (uint32_t i = lane; i < np; i += GS_WAVE) {
-        sk[i] = i < n ? skey[start + i] : kKeyMax;
-        sv[i] = i < n ? sval[start + i] : 0u;
+        sk[i] = i < n ? rec_key(skey[start + i]) : kKeyMax;
     }
     wave_sync();
     for (uint32_t k = 2; k <= np; k <<= 1) {
@@ -648,17 +663,14 @@ __device__ void wave_sort_tile64(uint32_t t, uint32_t start, uint32_t n, const u
                 const uint32_t q = i ^ mask;
                 const unsigned long long a = sk[i], b = sk[q];
                 if (b < a) {
-                    const uint32_t pa = sv[i], pb = sv[q];
                     sk[i] = b;
                     sk[q] = a;
-                    sv[i] = pb;
-                    sv[q] = pa;
                 }
             }
             wave_sync();
         }
     }
-    for (uint32_t i = lane; i < n; i += GS_WAVE) put_sorted(t, start + i, sk[i], sv[i], pair_emit, vals, keys64);
+    for (uint32_t i = lane; i < n; i += GS_WAVE) put_sorted(t, start + i, sk[i], pvals, pair_emit, vals, keys64);
     wave_sync();
 }
 
@@ -753,25 +765,27 @@ __device__ __forceinline__ void net32(uint32_t (&v)[K], uint32_t (&p)[K], uint32
     }
 }
 
-// Depth bits and emission position of key i (its high and low words).
-__device__ __forceinline__ uint32_t key_depth(const unsigned long long* __restrict__ skey, uint32_t i) {
-    return reinterpret_cast<const uint32_t*>(skey)[2 * (size_t)i + 1];
+// Depth bits and emission position of the key of record i (its high and low words).
+__device__ __forceinline__ uint32_t key_depth(const PairRec* __restrict__ skey, uint32_t i) {
+    return skey[i].depth;
 }
-__device__ __forceinline__ uint32_t key_emit(const unsigned long long* __restrict__ skey, uint32_t i) {
-    return reinterpret_cast<const uint32_t*>(skey)[2 * (size_t)i];
+__device__ __forceinline__ uint32_t key_emit(const PairRec* __restrict__ skey, uint32_t i) {
+    return skey[i].emit;
 }
 
 // Writes the pairs of a tile sorted by depth bits: sorted pair i is slot p.
 __device__ __forceinline__ void put_by_slot(uint32_t t, uint32_t start, uint32_t i, uint32_t depth, uint32_t p,
-                                            const unsigned long long* __restrict__ skey,
-                                            const uint32_t* __restrict__ sval, uint32_t* __restrict__ pair_emit,
-                                            uint32_t* __restrict__ vals, uint64_t* __restrict__ keys64) {
-    put_sorted(t, start + i, ((unsigned long long)depth << 32) | key_emit(skey, start + p), sval[start + p], pair_emit,
-               vals, keys64);
+                                            const PairRec* __restrict__ skey,
+                                            uint32_t* __restrict__ pair_emit, uint32_t* __restrict__ vals,
+                                            uint64_t* __restrict__ keys64) {
+    const PairRec r = skey[start + p];
+    vals[start + i] = r.gid;
+    pair_emit[start + i] = r.emit;
+    if (keys64) keys64[start + i] = ((uint64_t)t << 32) | depth;
 }
 
 // Runs of equal depth bits.  sk[0..n) holds a tile's keys in the order of
-// their depth bits (ties in any order), sv their primitives.  long_run: some
+// their depth bits (ties in any order).  long_run: some
 // run is longer than kRunMax (then entry i and entry i - kRunMax share their
 // depth bits).  place_runs writes sorted pair i for i = first, first + step,
 // ..: an entry outside a run stays at i; one inside a run [a, b) goes to a +
@@ -785,7 +799,7 @@ __device__ __forceinline__ bool long_run(const unsigned long long* sk, uint32_t 
 }
 
 __device__ __forceinline__ void place_runs(uint32_t t, uint32_t start, uint32_t n, const unsigned long long* sk,
-                                           const uint32_t* sv, uint32_t first, uint32_t step,
+                                           const uint32_t* __restrict__ pvals, uint32_t first, uint32_t step,
                                            uint32_t* __restrict__ pair_emit, uint32_t* __restrict__ vals,
                                            uint64_t* __restrict__ keys64) {
     for (uint32_t i = first; i < n; i += step) {
@@ -796,7 +810,7 @@ __device__ __forceinline__ void place_runs(uint32_t t, uint32_t start, uint32_t 
         while (b < n && hi32(sk[b]) == d) ++b;
         uint32_t at = a;
         for (uint32_t j = a; j < b; ++j) at += sk[j] < k ? 1u : 0u;
-        put_sorted(t, start + at, k, sv[i], pair_emit, vals, keys64);
+        put_sorted(t, start + at, k, pvals, pair_emit, vals, keys64);
     }
 }
 
@@ -804,8 +818,8 @@ __device__ __forceinline__ void place_runs(uint32_t t, uint32_t start, uint32_t 
 // registers, else wave_sort_tile64 in the wave's LDS.
 template <int K>
 __device__ __forceinline__ void wave_sort_tile(uint32_t t, uint32_t start, uint32_t n,
-                                               const unsigned long long* __restrict__ skey,
-                                               const uint32_t* __restrict__ sval, unsigned long long* sk, uint32_t* sv,
+                                               const PairRec* __restrict__ skey,
+                                               const uint32_t* __restrict__ pvals, unsigned long long* sk,
                                                uint32_t* __restrict__ pair_emit, uint32_t* __restrict__ vals,
                                                uint64_t* __restrict__ keys64) {
     const uint32_t lane = lane_id();
@@ -828,31 +842,28 @@ __device__ __forceinline__ void wave_sort_tile(uint32_t t, uint32_t start, uint3
         tie |= lane + 1 < GS_WAVE && (lane + 1) * K < n && v[K - 1] == next;
     }
     if (__ballot(odd) != 0ull) {
-        wave_sort_tile64(t, start, n, skey, sval, sk, sv, pair_emit, vals, keys64);
+        wave_sort_tile64(t, start, n, skey, pvals, sk, pair_emit, vals, keys64);
         return;
     }
     if (__ballot(tie) == 0ull) {
 #pragma unroll
         for (int r = 0; r < K; ++r)
-            if (lane * K + r < n) put_by_slot(t, start, lane * K + r, v[r], p[r], skey, sval, pair_emit, vals, keys64);
+            if (lane * K + r < n) put_by_slot(t, start, lane * K + r, v[r], p[r], skey, pair_emit, vals, keys64);
         return;
     }
     // equal depth bits: the sorted keys to LDS, then each run placed by emission position
 #pragma unroll
     for (int r = 0; r < K; ++r) {
         const uint32_t i = lane * K + r;
-        if (i < n) {
-            sk[i] = ((unsigned long long)v[r] << 32) | key_emit(skey, start + p[r]);
-            sv[i] = sval[start + p[r]];
-        }
+        if (i < n) sk[i] = ((unsigned long long)v[r] << 32) | key_emit(skey, start + p[r]);
     }
     wave_sync();
     if (__ballot(long_run(sk, n, lane, GS_WAVE)) != 0ull) {
         wave_sync();
-        wave_sort_tile64(t, start, n, skey, sval, sk, sv, pair_emit, vals, keys64);
+        wave_sort_tile64(t, start, n, skey, pvals, sk, pair_emit, vals, keys64);
         return;
     }
-    place_runs(t, start, n, sk, sv, lane, GS_WAVE, pair_emit, vals, keys64);
+    place_runs(t, start, n, sk, pvals, lane, GS_WAVE, pair_emit, vals, keys64);
     wave_sync();
 }
 
@@ -867,15 +878,13 @@ constexpr uint32_t kLongCap = GS_BLOCK * kLongK;
 constexpr uint32_t kDepthSortBlocksPerCU = 8;
 
 // The exact network over the n (<= kLongCap) 64-bit keys skey[start ..
-// start + n) by the whole workgroup in LDS: sorted keys in sk[0..n), their
-// primitives in sv.
-__device__ void block_sort_lds64(uint32_t start, uint32_t n, const unsigned long long* __restrict__ skey,
-                                 const uint32_t* __restrict__ sval, unsigned long long* sk, uint32_t* sv) {
+// start + n) by the whole workgroup in LDS: sorted keys in sk[0..n).
+__device__ void block_sort_lds64(uint32_t start, uint32_t n, const PairRec* __restrict__ skey,
+                                 unsigned long long* sk) {
     uint32_t np = 2;
     while (np < n) np <<= 1;
     for (uint32_t i = threadIdx.x; i < np; i += GS_BLOCK) {
-        sk[i] = i < n ? skey[start + i] : kKeyMax;
-        sv[i] = i < n ? sval[start + i] : 0u;
+        sk[i] = i < n ? rec_key(skey[start + i]) : kKeyMax;
     }
     __syncthreads();
     for (uint32_t k = 2; k <= np; k <<= 1) {
@@ -886,11 +895,8 @@ __device__ void block_sort_lds64(uint32_t start, uint32_t n, const unsigned long
                 const uint32_t q = i ^ mask;
                 const unsigned long long a = sk[i], b = sk[q];
                 if (b < a) {
-                    const uint32_t pa = sv[i], pb = sv[q];
                     sk[i] = b;
                     sk[q] = a;
-                    sv[i] = pb;
-                    sv[q] = pa;
                 }
             }
             __syncthreads();
@@ -900,12 +906,12 @@ __device__ void block_sort_lds64(uint32_t start, uint32_t n, const unsigned long
 
 // The exact network over the n (<= kLongCap) 64-bit keys of a tile by the
 // whole workgroup in LDS, written out in order.
-__device__ void block_sort_tile64(uint32_t t, uint32_t start, uint32_t n, const unsigned long long* __restrict__ skey,
-                                  const uint32_t* __restrict__ sval, unsigned long long* sk, uint32_t* sv,
+__device__ void block_sort_tile64(uint32_t t, uint32_t start, uint32_t n, const PairRec* __restrict__ skey,
+                                  const uint32_t* __restrict__ pvals, unsigned long long* sk,
                                   uint32_t* __restrict__ pair_emit, uint32_t* __restrict__ vals,
                                   uint64_t* __restrict__ keys64) {
-    block_sort_lds64(start, n, skey, sval, sk, sv);
-    for (uint32_t i = threadIdx.x; i < n; i += GS_BLOCK) put_sorted(t, start + i, sk[i], sv[i], pair_emit, vals, keys64);
+    block_sort_lds64(start, n, skey, sk);
+    for (uint32_t i = threadIdx.x; i < n; i += GS_BLOCK) put_sorted(t, start + i, sk[i], pvals, pair_emit, vals, keys64);
     __syncthreads();
 }
 
@@ -937,74 +943,66 @@ constexpr int kRankGroup = 4;
 // The keys of run [r0, r0 + m) of the segment, ranked in the ascending keys
 // sk[0..mo) in LDS; key i of the run goes to r_out + i + its rank.
 __device__ __forceinline__ void place_ranked(uint32_t t, uint32_t start, uint32_t r0, uint32_t m, uint32_t r_out,
-                                             const unsigned long long* __restrict__ skey,
-                                             const uint32_t* __restrict__ sval, const unsigned long long* sk,
+                                             const PairRec* __restrict__ skey,
+                                             const uint32_t* __restrict__ pvals, const unsigned long long* sk,
                                              uint32_t mo, uint32_t* __restrict__ pair_emit,
                                              uint32_t* __restrict__ vals, uint64_t* __restrict__ keys64) {
     constexpr uint32_t kGroupSpan = kRankGroup * GS_BLOCK;
 #pragma unroll 1
     for (uint32_t g = 0; g < m; g += kGroupSpan) {
         unsigned long long kk[kRankGroup];
-        uint32_t pk[kRankGroup], rk[kRankGroup];
+        uint32_t rk[kRankGroup];
 #pragma unroll
         for (int k = 0; k < kRankGroup; ++k) {
             const uint32_t i = min(g + threadIdx.x + k * GS_BLOCK, m - 1u);
-            kk[k] = skey[start + r0 + i];
-            pk[k] = sval[start + r0 + i];
+            kk[k] = rec_key(skey[start + r0 + i]);
         }
         rank_in<kRankGroup>(sk, mo, kk, rk);
 #pragma unroll
         for (int k = 0; k < kRankGroup; ++k) {
             const uint32_t i = g + threadIdx.x + k * GS_BLOCK;
-            if (i < m) put_sorted(t, start + r_out + i + rk[k], kk[k], pk[k], pair_emit, vals, keys64);
+            if (i < m) put_sorted(t, start + r_out + i + rk[k], kk[k], pvals, pair_emit, vals, keys64);
         }
     }
 }
 
-__device__ void sort_two_runs(uint32_t t, uint32_t start, uint32_t n, unsigned long long* __restrict__ skey,
-                              uint32_t* __restrict__ sval, unsigned long long* sk, uint32_t* sv,
+__device__ void sort_two_runs(uint32_t t, uint32_t start, uint32_t n, PairRec* __restrict__ skey,
+                              const uint32_t* __restrict__ pvals, unsigned long long* sk,
                               uint32_t* __restrict__ pair_emit, uint32_t* __restrict__ vals,
                               uint64_t* __restrict__ keys64) {
     const uint32_t tid = threadIdx.x;
     const uint32_t na = kLongCap, nb = n - kLongCap;
     // the first run sorted, to its place
-    block_sort_lds64(start, na, skey, sval, sk, sv);
-    for (uint32_t i = tid; i < na; i += GS_BLOCK) {
-        skey[start + i] = sk[i];
-        sval[start + i] = sv[i];
-    }
+    block_sort_lds64(start, na, skey, sk);
+    for (uint32_t i = tid; i < na; i += GS_BLOCK) put_key(&skey[start + i], sk[i]);
     __threadfence_block();
     __syncthreads();
     // the second run sorted (in LDS); the first run's keys placed by their ranks in it
-    block_sort_lds64(start + na, nb, skey, sval, sk, sv);
-    place_ranked(t, start, 0u, na, 0u, skey, sval, sk, nb, pair_emit, vals, keys64);
+    block_sort_lds64(start + na, nb, skey, sk);
+    place_ranked(t, start, 0u, na, 0u, skey, pvals, sk, nb, pair_emit, vals, keys64);
     // the second run to its place, the first back to LDS; the second run's keys placed
-    for (uint32_t i = tid; i < nb; i += GS_BLOCK) {
-        skey[start + na + i] = sk[i];
-        sval[start + na + i] = sv[i];
-    }
+    for (uint32_t i = tid; i < nb; i += GS_BLOCK) put_key(&skey[start + na + i], sk[i]);
     __threadfence_block();
     __syncthreads();
-    for (uint32_t i = tid; i < na; i += GS_BLOCK) sk[i] = skey[start + i];
+    for (uint32_t i = tid; i < na; i += GS_BLOCK) sk[i] = rec_key(skey[start + i]);
     __syncthreads();
-    place_ranked(t, start, na, nb, 0u, skey, sval, sk, na, pair_emit, vals, keys64);
+    place_ranked(t, start, na, nb, 0u, skey, pvals, sk, na, pair_emit, vals, keys64);
     __syncthreads();
 }
 
 // A tile by the whole workgroup, exactly: up to 2 kLongCap pairs as two runs
 // in LDS, longer ones in place in global memory.
-__device__ void sort_huge_tile(uint32_t t, uint32_t start, uint32_t n, unsigned long long* __restrict__ skey,
-                               uint32_t* __restrict__ sval, unsigned long long* sk, uint32_t* sv,
+__device__ void sort_huge_tile(uint32_t t, uint32_t start, uint32_t n, PairRec* __restrict__ skey,
+                               const uint32_t* __restrict__ pvals, unsigned long long* sk,
                                uint32_t* __restrict__ pair_emit, uint32_t* __restrict__ vals,
                                uint64_t* __restrict__ keys64) {
     if (n <= 2 * kLongCap) {
-        sort_two_runs(t, start, n, skey, sval, sk, sv, pair_emit, vals, keys64);
+        sort_two_runs(t, start, n, skey, pvals, sk, pair_emit, vals, keys64);
         return;
     }
-    unsigned long long* key = skey + start;
-    uint32_t* val = sval + start;
-    bitonic_global(key, val, n);
-    for (uint32_t i = threadIdx.x; i < n; i += GS_BLOCK) put_sorted(t, start + i, key[i], val[i], pair_emit, vals, keys64);
+    PairRec* key = skey + start;
+    bitonic_global(key, n);
+    for (uint32_t i = threadIdx.x; i < n; i += GS_BLOCK) put_sorted(t, start + i, rec_key(key[i]), pvals, pair_emit, vals, keys64);
 }
 
 // One cross-wave step of a long tile: element i (register r of lane l of
@@ -1035,8 +1033,8 @@ __device__ __forceinline__ void long_exchange(uint32_t (&v)[K], uint32_t (&p)[K]
 
 // A long tile (at most 256 K pairs) by the whole workgroup, K keys a lane.
 template <int K>
-__device__ __forceinline__ void sort_long_tile(uint32_t t, uint32_t start, uint32_t n, unsigned long long* __restrict__ skey,
-                               uint32_t* __restrict__ sval, unsigned long long* s_kv, uint32_t* s_v,
+__device__ __forceinline__ void sort_long_tile(uint32_t t, uint32_t start, uint32_t n, PairRec* __restrict__ skey,
+                               const uint32_t* __restrict__ pvals, unsigned long long* s_kv,
                                uint32_t* s_first, uint32_t* __restrict__ pair_emit, uint32_t* __restrict__ vals,
                                uint64_t* __restrict__ keys64) {
     const uint32_t w = threadIdx.x / GS_WAVE, lane = lane_id();
@@ -1055,7 +1053,7 @@ __device__ __forceinline__ void sort_long_tile(uint32_t t, uint32_t start, uint3
         odd |= act && i < n && v[r] == kDepthPad;
     }
     if (__syncthreads_or(odd)) {
-        block_sort_tile64(t, start, n, skey, sval, s_kv, s_v, pair_emit, vals, keys64);
+        block_sort_tile64(t, start, n, skey, pvals, s_kv, pair_emit, vals, keys64);
         return;
     }
     if (act) net32<K, (int)kWave>(v, p, lane);
@@ -1081,7 +1079,7 @@ __device__ __forceinline__ void sort_long_tile(uint32_t t, uint32_t start, uint3
         if (act) {
 #pragma unroll
             for (int r = 0; r < K; ++r)
-                if (ibase + r < n) put_by_slot(t, start, ibase + r, v[r], p[r], skey, sval, pair_emit, vals, keys64);
+                if (ibase + r < n) put_by_slot(t, start, ibase + r, v[r], p[r], skey, pair_emit, vals, keys64);
         }
         return;
     }
@@ -1090,18 +1088,15 @@ __device__ __forceinline__ void sort_long_tile(uint32_t t, uint32_t start, uint3
 #pragma unroll
         for (int r = 0; r < K; ++r) {
             const uint32_t i = ibase + r;
-            if (i < n) {
-                s_kv[i] = ((unsigned long long)v[r] << 32) | key_emit(skey, start + p[r]);
-                s_v[i] = sval[start + p[r]];
-            }
+            if (i < n) s_kv[i] = ((unsigned long long)v[r] << 32) | key_emit(skey, start + p[r]);
         }
     }
     __syncthreads();
     if (__syncthreads_or(long_run(s_kv, n, threadIdx.x, GS_BLOCK))) {
-        block_sort_tile64(t, start, n, skey, sval, s_kv, s_v, pair_emit, vals, keys64);
+        block_sort_tile64(t, start, n, skey, pvals, s_kv, pair_emit, vals, keys64);
         return;
     }
-    place_runs(t, start, n, s_kv, s_v, threadIdx.x, GS_BLOCK, pair_emit, vals, keys64);
+    place_runs(t, start, n, s_kv, pvals, threadIdx.x, GS_BLOCK, pair_emit, vals, keys64);
     __syncthreads();
 }
 
@@ -1114,13 +1109,12 @@ __device__ __forceinline__ void sort_long_tile(uint32_t t, uint32_t start, uint3
 template <bool FEW>
 __global__ void __launch_bounds__(GS_BLOCK) k_tile_depth_sort(const uint4* __restrict__ rec,
                                                               const uint32_t* __restrict__ n_long_ptr, uint32_t T,
-                                                              unsigned long long* __restrict__ skey,
-                                                              uint32_t* __restrict__ sval,
+                                                              PairRec* __restrict__ skey,
+                                                              const uint32_t* __restrict__ pvals,
                                                               uint32_t* __restrict__ pair_emit,
                                                               uint32_t* __restrict__ vals,
                                                               uint64_t* __restrict__ keys64) {
     __shared__ unsigned long long s_kv[kLongCap];      // long tiles; a quarter per wave otherwise
-    __shared__ uint32_t s_v[kLongCap];
     __shared__ uint32_t s_first[kSortWaves];
     const uint32_t G = gridDim.x;                             // <= T
     const uint32_t w = threadIdx.x / GS_WAVE;
@@ -1135,35 +1129,34 @@ __global__ void __launch_bounds__(GS_BLOCK) k_tile_depth_sort(const uint4* __res
     for (uint32_t pos = blockIdx.x; pos < n_long; pos += G) {
         if (pos != blockIdx.x) rl = rec[pos];
         if (FEW && rl.z <= 2u * GS_BLOCK)
-            sort_long_tile<2>(rl.x, rl.y, rl.z, skey, sval, s_kv, s_v, s_first, pair_emit, vals, keys64);
+            sort_long_tile<2>(rl.x, rl.y, rl.z, skey, pvals, s_kv, s_first, pair_emit, vals, keys64);
         else if (FEW && rl.z <= 4u * GS_BLOCK)
-            sort_long_tile<4>(rl.x, rl.y, rl.z, skey, sval, s_kv, s_v, s_first, pair_emit, vals, keys64);
+            sort_long_tile<4>(rl.x, rl.y, rl.z, skey, pvals, s_kv, s_first, pair_emit, vals, keys64);
         else if (rl.z <= kLongCap)
-            sort_long_tile<8>(rl.x, rl.y, rl.z, skey, sval, s_kv, s_v, s_first, pair_emit, vals, keys64);
+            sort_long_tile<8>(rl.x, rl.y, rl.z, skey, pvals, s_kv, s_first, pair_emit, vals, keys64);
         else
-            sort_huge_tile(rl.x, rl.y, rl.z, skey, sval, s_kv, s_v, pair_emit, vals, keys64);
+            sort_huge_tile(rl.x, rl.y, rl.z, skey, pvals, s_kv, pair_emit, vals, keys64);
     }
     unsigned long long* sk = s_kv + w * (kLongCap / kSortWaves);
-    uint32_t* sv = s_v + w * (kLongCap / kSortWaves);
     for (uint32_t s = s0; s < T - n_long; s += kSortWaves * G) {
         if (s != s0) rs = rec[n_long + s];
         const uint32_t t = rs.x, start = rs.y, n = rs.z;
         if (n == 0u || n >= kWaveSortMax<FEW>) continue;     // (the order puts every longer tile first)
         if (n <= 64u)
-            wave_sort_tile<1>(t, start, n, skey, sval, sk, sv, pair_emit, vals, keys64);
+            wave_sort_tile<1>(t, start, n, skey, pvals, sk, pair_emit, vals, keys64);
         else if (n <= 128u)
-            wave_sort_tile<2>(t, start, n, skey, sval, sk, sv, pair_emit, vals, keys64);
+            wave_sort_tile<2>(t, start, n, skey, pvals, sk, pair_emit, vals, keys64);
         else if (FEW || n <= 256u)
-            wave_sort_tile<4>(t, start, n, skey, sval, sk, sv, pair_emit, vals, keys64);
+            wave_sort_tile<4>(t, start, n, skey, pvals, sk, pair_emit, vals, keys64);
         else
-            wave_sort_tile<8>(t, start, n, skey, sval, sk, sv, pair_emit, vals, keys64);
+            wave_sort_tile<8>(t, start, n, skey, pvals, sk, pair_emit, vals, keys64);
     }
 }
 
 struct BinsortLayout {
     size_t pkeys, emit_id;    // per emission position: tile and primitive of the pair
     size_t pdepth;            // per emission position: the primitive's depth bits
-    size_t skey, sval;        // per sorted position: the 64-bit depth-sort key and its primitive
+    size_t skey;              // per sorted position, a record: the 64-bit depth-sort key, the primitive
     size_t order;             // the dispatch order when the caller keeps none
     size_t rec;               // per dispatch position: tile, range start, pair count
     size_t tcount, cursor;    // per tile: pair total, placement cursor
@@ -1184,8 +1177,7 @@ BinsortLayout binsort_layout(int32_t n, uint32_t capacity, int32_t width, int32_
     L.pkeys = o; o += align256(4 * cc);
     L.emit_id = o; o += align256(4 * cc);
     L.pdepth = o; o += align256(4 * cc);
-    L.skey = o; o += align256(8 * cc);
-    L.sval = o; o += align256(4 * cc);
+    L.skey = o; o += align256(sizeof(PairRec) * cc);
     L.order = o; o += align256(4 * tt);
     L.rec = o; o += align256(16 * tt);
     L.tcount = o; o += align256(4 * tt);
@@ -1259,18 +1251,18 @@ hipError_t launch_binsort(const gs_proj& proj, int32_t n, const uint32_t* vis_id
     e = finish();
     if (e != hipSuccess) return e;
     // 4. every pair's depth-sort key placed in its tile's range
-    unsigned long long* skey = at<unsigned long long>(ws, L.skey);
-    uint32_t* sval = at<uint32_t>(ws, L.sval);
+    PairRec* skey = at<PairRec>(ws, L.skey);
+    const uint32_t* pvals = at<uint32_t>(ws, L.emit_id);
     hipLaunchKernelGGL(k_tile_scatter, dim3(nbp), dim3(GS_BLOCK), 0, st, at<uint32_t>(ws, L.pkeys),
-                       at<uint32_t>(ws, L.emit_id), at<uint32_t>(ws, L.pdepth), ctr + 1, T, cursor, skey, sval);
+                       pvals, at<uint32_t>(ws, L.pdepth), ctr + 1, T, cursor, skey);
     // 5. per tile, longest first: depth order, primitive ids (+ optional 64-bit keys)
     const dim3 grid(std::min<uint32_t>(T, cus * kDepthSortBlocksPerCU));
     if (few)
         hipLaunchKernelGGL(k_tile_depth_sort<true>, grid, dim3(GS_BLOCK), 0, st, at<uint4>(ws, L.rec), ctr + 2, T, skey,
-                           sval, pair_emit, vals, keys);
+                           pvals, pair_emit, vals, keys);
     else
         hipLaunchKernelGGL(k_tile_depth_sort<false>, grid, dim3(GS_BLOCK), 0, st, at<uint4>(ws, L.rec), ctr + 2, T, skey,
-                           sval, pair_emit, vals, keys);
+                           pvals, pair_emit, vals, keys);
     return hipGetLastError();
 }
 
