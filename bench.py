@@ -427,7 +427,7 @@ def run_workload(name, steps, warmup, overlap=True, packed=True, row_major=False
     log("%s phase rooflines: " % w.name + json.dumps(per_phase))
     wi_mean = float(np.mean([w_iters[v] for v in views]))
     wh_mean = float(np.mean([w_hits[v] for v in views]))
-    log("%s mean per view: V=%.0f M=%.0f evaluated=%.3g included=%.3g; forward (pixel row, pair) steps %.3g, "
+    log("%s mean per view: V=%.0f M=%.0f evaluated=%.3g included=%.3g; forward (16-pixel strip, pair) steps %.3g, "
         "with an included pixel %.3g (%.1f%%), included lanes per such step %.1f of 16"
         % (w.name, V_mean, M_mean, ev_mean, inc_mean, wi_mean, wh_mean, 100 * wh_mean / max(wi_mean, 1),
            inc_mean / max(wh_mean, 1)))
