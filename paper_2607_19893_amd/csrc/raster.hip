@@ -49,26 +49,35 @@ struct __align__(16) Splat {
     float o, r, g, b;
 };
 
-// A pair is skipped where sigma < 0.  That can only happen if its conic is not
-// positive definite (kIndefinite): the walks test it in batches that hold such a
-// pair.  The polynomial's rounding is below 1e-10, so a zero of sigma can come out
-// as a tiny negative number.  kCapped marks an opacity above the 0.99 cap of alpha, at
-// which the backward's derivatives of alpha vanish.
-constexpr float kSigmaNeg = -1e-9f;
-constexpr uint32_t kIndefinite = 1u << 16, kCapped = 1u << 17;
+// A pair is skipped where sigma < 0, which its exact sigma is only if its conic is not
+// positive definite.  The polynomial's rounding error is at most 16 * 2^-53 of
+//   size = A/2 x^2 + |B| x y + C/2 y^2,  (x, y) = (|u| + 7.5, |v| + 7.5),
+// (u, v) the centre from the tile's: nine roundings on the way to the coefficients
+// and five of the evaluation, each of a sum of terms that lie within size.  Up to
+// kNearSize that is below 5e-9: a definite pair's sigma neither overflows nor makes
+// exp(-sigma) round above 1, and needs no test.  Batches that hold another pair
+// (kChecked) test sigma.  An indefinite pair, whose record carries -o, is skipped below
+// kSigmaNeg (a zero of sigma can come out as a tiny negative number).  A definite pair
+// further out has its negative sigmas, which are rounding, taken as 0, and those beyond
+// kSigmaFar, possibly past the fp32 range, as kSigmaFar, at which alpha is 0.  kCapped
+// marks an opacity above the 0.99 cap of alpha, at which the backward's derivatives of
+// alpha vanish.
+constexpr float kSigmaNeg = -1e-9f, kSigmaFar = 1e4f, kNearSize = 2.5e6f;
+constexpr uint32_t kChecked = 1u << 16, kCapped = 1u << 17;
 
 // Fills rec from a pair's mean, conic and colour, relative to the tile centre
 // (xc, yc), and returns the tile's blocks of 8 x BH pixels that hold a pixel centre
 // with sigma <= cut = ln(255 o) + kCutMargin: a block that is left out has no pixel
 // at or above alpha = 1/255.  Bit b is the block of wave b / (8 / BH) (quadrant
-// (w & 1, w >> 1)), counted downwards inside the quadrant; kIndefinite and kCapped
+// (w & 1, w >> 1)), counted downwards inside the quadrant; kChecked and kCapped
 // come on top.
 //
 // sigma's minimum over a rectangle lies at its centre if that is inside, else on
 // the vertical or horizontal edge line nearest to the centre: along each of the
 // two lines it is at the line's vertex clamped to the rectangle.  In fp32, with
 // the rounding of sigma's terms (bounded by their largest values over the tile)
-// added to the cut.  A conic that is not positive definite reaches every block.
+// added to the cut.  A conic that is not positive definite reaches every block, an
+// infinite centre or conic none.
 template <int BH>
 __device__ __forceinline__ uint32_t stage_pair(Splat* rec, float2 m, float4 co, const float* __restrict__ rgb3,
                                                double xc, double yc) {
@@ -91,15 +100,23 @@ __device__ __forceinline__ uint32_t stage_pair(Splat* rec, float2 m, float4 co, 
     const float cut = fmaf(__builtin_amdgcn_logf(255.0f * co.w), kLn2, kCutMargin);
     if (!(cut > 0.0f)) return 0u;              // opacity below 1/255: no pixel can take it
     const float A = co.x, B = co.y, C = co.z, u = (float)du, v = (float)dv;
-    if (!(A > 0.0f) || !((double)A * C - (double)B * B > 0.0)) {
-        const bool nan = u != u || v != v || (A > 0.0f && (B != B || C != C));
-        return nan ? 0u : kAll | kIndefinite | kCapped;
+    const float hA = 0.5f * A, hC = 0.5f * C;
+    const float mx = fabsf(u) + 7.5f, my = fabsf(v) + 7.5f;
+    const float size = hA * mx * mx + fabsf(B) * mx * my + hC * my * my;
+    const float lim = fmaf(1e-6f, size, cut);
+    const bool definite = A > 0.0f && (double)A * C - (double)B * B > 0.0;
+    uint32_t mask = co.w > kAlphaMax ? kCapped : 0u;
+    if (!definite || !(size <= kNearSize)) {
+        if (isinf(u) || isinf(v) || isinf(A) || isinf(B) || isinf(C)) return 0u;
+        mask = kChecked | kCapped;
+        if (!definite) {
+            const bool nan = u != u || v != v || (A > 0.0f && (B != B || C != C));
+            rec->o = -co.w;
+            return nan ? 0u : kAll | mask;
+        }
+        if (isinf(lim)) return kAll | mask;
     }
     const float sx = -B * __builtin_amdgcn_rcpf(A), sy = -B * __builtin_amdgcn_rcpf(C);
-    const float mx = fabsf(u) + 7.5f, my = fabsf(v) + 7.5f;
-    const float hA = 0.5f * A, hC = 0.5f * C;
-    const float lim = fmaf(1e-6f, hA * mx * mx + fabsf(B) * mx * my + hC * my * my, cut);
-    uint32_t mask = co.w > kAlphaMax ? kCapped : 0u;
 #pragma unroll
     for (int r = 0; r < 2 * kPer; ++r) {
         // offsets (splat - pixel) over the block's rows and columns
@@ -135,6 +152,15 @@ struct PixelPoly {
     }
 };
 
+// sigma of a staged pair, for a batch whose pairs need a test (see kChecked): false
+// if the pair is skipped; o is set to its opacity.  A NaN stays one.
+__device__ __forceinline__ bool check_sigma(const Splat& S, float& sigma, float& o) {
+    const bool skip = S.o < 0.0f && sigma < kSigmaNeg;
+    o = fabsf(S.o);
+    sigma = sigma > kSigmaFar ? kSigmaFar : (sigma < 0.0f ? 0.0f : sigma);
+    return !skip;
+}
+
 // Pairs a walk takes per iteration; the lists are padded to a multiple of it.
 constexpr int kPad = 4;
 
@@ -164,8 +190,8 @@ __device__ __forceinline__ uint32_t quad_list(const uint8_t* quad, uint32_t* lis
 // 2^-t = 2^-hi * 2^-lo with 2^-lo = 1 - lo ln2 up to (lo ln2)^2 / 2 < 1e-10;
 // the hardware base-2 exponential (1 ulp) takes -hi directly.  About two ulps
 // in all, far inside the alpha decision band; forward and backward call the
-// same code, so they take identical decisions.  Very large sigmas give 0,
-// negative ones are rejected by the caller.
+// same code, so they take identical decisions.  Sigmas from 104 on give 0; past 2.3e38
+// hi overflows and the result is a NaN, which the caller's kSigmaFar keeps out.
 __device__ __forceinline__ float exp_neg(float sigma) {
     constexpr float kLog2eHi = 1.44269502162933349609375f;    // log2(e) rounded to fp32
     constexpr float kLog2eLo = 1.925963033500011e-08f;        // log2(e) - kLog2eHi
@@ -254,7 +280,7 @@ __global__ void __launch_bounds__(GS_BLOCK, STATS ? 5 : 6) k_raster_fwd(
         if (j + GS_BLOCK < end) g = vals[j + GS_BLOCK];
         s_quad[tid] = (uint8_t)quad;
         s_hit[tid] = 0;
-        const bool check = __syncthreads_or((int)(quad & kIndefinite));
+        const bool check = __syncthreads_or((int)(quad & kChecked));
         if (__ballot(T > 0.0f) != 0ull) {
             const uint32_t n_list = quad_list(s_quad, s_list[w], min((uint32_t)GS_BLOCK, end - bs), w);
             uint32_t lk = 0xFFFFFFFFu;      // record offset of the pixel's last included pair of this batch
@@ -270,13 +296,14 @@ __global__ void __launch_bounds__(GS_BLOCK, STATS ? 5 : 6) k_raster_fwd(
                     for (int i = 0; i < kPad; ++i) {
                         const uint32_t at = ats[i];
                         const Splat& S = *reinterpret_cast<const Splat*>(reinterpret_cast<const char*>(L) + at);
-                        const float sigma = P.eval(S);
-                        float al = fminf(kAlphaMax, S.o * exp_neg(sigma));
+                        float sigma = P.eval(S), o = S.o;
+                        const bool on = !CHECK || check_sigma(S, sigma, o);
+                        float al = fminf(kAlphaMax, o * exp_neg(sigma));
                         uint64_t ok_mask = __builtin_amdgcn_ballot_w64(!(al < kAlphaMin));
                         bool ok = !(al < kAlphaMin);
                         if (CHECK) {
-                            ok_mask &= __builtin_amdgcn_ballot_w64(!(sigma < kSigmaNeg));
-                            ok = ok & !(sigma < kSigmaNeg);
+                            ok_mask &= __builtin_amdgcn_ballot_w64(on);
+                            ok = ok & on;
                         }
                         al = ok ? al : 0.0f;
                         const float Tn = T * (1.0f - al);
@@ -622,7 +649,7 @@ __global__ void __launch_bounds__(GS_BLOCK, 4) k_raster_bwd(
                 s_v[lane] = (float)((double)m.y - yc);
                 s_mask[lane] = (uint16_t)mask;
                 s_emit[lane] = emit;
-                const uint64_t sp = __ballot((mask & (kIndefinite | kCapped)) != 0u);
+                const uint64_t sp = __ballot((mask & (kChecked | kCapped)) != 0u);
                 if (lane == 0) s_special = sp != 0ull ? 1u : 0u;
             }
             __syncthreads();
@@ -658,12 +685,13 @@ __global__ void __launch_bounds__(GS_BLOCK, 4) k_raster_bwd(
                         const uint32_t at = i ? at2 >> 16 : at2 & 0xFFFFu;
                         const Splat& S = *reinterpret_cast<const Splat*>(reinterpret_cast<const char*>(L) + 2 * at);
                         const float u = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(s_u) + at / kSums);
-                        const float sigma = P.eval(S);
-                        const float gv = S.o * exp_neg(sigma);
+                        float sigma = P.eval(S), o = S.o;
+                        const bool on = !CHECK || check_sigma(S, sigma, o);
+                        const float gv = o * exp_neg(sigma);
                         float al = CHECK ? fminf(kAlphaMax, gv) : gv;
                         // a lane without the pair takes alpha = 0: its T stays, its weight and ds are 0
                         bool ok = (at < last_b) & !(al < kAlphaMin);
-                        if (CHECK) ok = ok & !(sigma < kSigmaNeg);
+                        if (CHECK) ok = ok & on;
                         al = ok ? al : 0.0f;
                         const float inv_om = __builtin_amdgcn_rcpf(1.0f - al);
                         T = T * inv_om;

@@ -302,3 +302,118 @@ def test_hazard_lists_over_many_blocks(n, torch_gpu, gs):
     np.testing.assert_array_equal(host_u32(counts), [r.size for r in ref] + [RB.size])
     for t, r in zip(ids, ref):
         np.testing.assert_array_equal(host_u32(t, r.size), r)
+
+
+def blend_arrays(torch, uv, con, op, rgb, depth, width, height, dL):
+    """The forward's and the backward's outputs of a caller's own projection arrays, every
+    pair in every tile's list."""
+    from paper_2607_19893_amd import scenes
+    from paper_2607_19893_amd.pipeline import ViewTrainer
+    n = len(op)
+    cam = scenes.look_at((0.0, 0.0, -4.0), (0.0, 0.0, 0.0), (0.0, -1.0, 0.0), width, height, 60.0)
+    tx, ty = (width + 15) // 16, (height + 15) // 16
+    tr = ViewTrainer(scenes.tiny(n=n).scene, capacity=n * tx * ty + 64, max_width=width, max_height=height,
+                     with_replica=False)
+    tr.project(cam)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    tr.tiles.copy_(dev(np.full(n, tx * ty, np.int32)))
+    tr.rect.copy_(dev(np.tile(np.array([0, 0, tx, ty], np.int16), (n, 1))))
+    tr.depth.copy_(dev(depth))
+    tr.mean2d.copy_(dev(uv))
+    tr.conic.copy_(dev(np.concatenate([con, op[:, None]], 1)))
+    tr.rgb.copy_(dev(rgb))
+    tr.clamp.zero_()
+    tr.visible()
+    tr.bin_sort()
+    tr.active.zero_()
+    tr.raster_fwd(active=True)
+    tr.set_dL(dL)
+    tr.raster_bwd(grad2d=True)
+    torch.cuda.synchronize()
+    assert tr.host_status()[0] == 0
+    hw = width * height
+    return dict(img=tr.img.view(-1)[:3 * hw].cpu().numpy().reshape(3, height, width),
+                final_T=tr.final_T.view(-1)[:hw].cpu().numpy(), n_contrib=host_u32(tr.n_contrib, hw),
+                active=tr.active.cpu().numpy()[:n], grad2d=tr.grad2d.cpu().numpy()[:n],
+                grad_rows=tr.grad_rows.cpu().numpy()[:n])
+
+
+def ordinary_pairs(rng, n, width, height):
+    """Centres, conics, opacities, colours of n definite footprints over the image."""
+    f32 = lambda a: np.ascontiguousarray(a, np.float32)  # noqa: E731
+    uv = rng.uniform(-6, 6, (n, 2)) + rng.random((n, 2)) * [width, height]
+    s1, s2 = np.exp(rng.uniform(-0.5, 2.5, n)), np.exp(rng.uniform(-0.5, 2.5, n))
+    c, s = np.cos(th := rng.uniform(0, np.pi, n)), np.sin(th)
+    con = np.stack([(c / s1) ** 2 + (s / s2) ** 2, c * s * (s1 ** -2 - s2 ** -2), (s / s1) ** 2 + (c / s2) ** 2], 1)
+    return f32(uv), f32(con), f32(rng.uniform(0.02, 0.3, n)), f32(rng.random((n, 3)))
+
+
+@pytest.mark.parametrize("n", [3, 400])
+def test_raster_far_centres(n, torch_gpu):
+    """Pairs whose sigma over the whole image is past every cut-off, up to the end of the
+    fp32 range and at infinite centres and conics, leave everything as if they had no
+    opacity, and get no gradient themselves."""
+    width, height = 37, 29
+    rng = np.random.default_rng(n)
+    uv, con, op, rgb = ordinary_pairs(rng, n, width, height)
+    inf, big = np.inf, np.float32(3.4e38)
+    far = [(u, v, A, B, C) for u, v in ((1e20, 3), (5, -1e20), (-2e19, 2e19), (inf, 4), (7, -inf), (inf, inf),
+                                        (big, -big), (1e12, 1e12), (-3e4, 3e4), (9, 5e3))
+           for A, B, C in ((1, 0, 1), (1, 0.5, 1), (3.3, -3.2, 3.3), (0.3, 0, 3.0))]
+    far += [(8, 8, *abc) for abc in ((inf, 0, 1), (1, inf, 1), (1, 0, inf), (big, 0, big), (inf, inf, inf),
+                                     (-inf, 0, 1), (0, 0, inf), (1, -inf, 1))]
+    far = np.array(far, np.float32)
+    far[(far[:, :2] == 8).all(1), :2] = [8.25, 8.25]      # (big, 0, big): off every pixel centre
+    k = len(far)
+    fop = np.resize(np.array([0.5, 0.99, 0.999, 0.05], np.float32), k)
+    at = rng.permutation(n + k)                             # far pairs anywhere in the depth order
+    join = lambda a, b: np.ascontiguousarray(np.concatenate([a, b])[at], np.float32)  # noqa: E731
+    depth = np.arange(1, n + k + 1, dtype=np.float32)
+    arrays = (join(uv, far[:, :2]), join(con, far[:, 2:]))
+    col = join(rgb, rng.random((k, 3)))
+    dL = rng.uniform(-1, 1, (3, height, width)).astype(np.float32)
+    got = blend_arrays(torch_gpu, *arrays, join(op, fop), col, depth, width, height, dL)
+    ref = blend_arrays(torch_gpu, *arrays, join(op, np.zeros(k)), col, depth, width, height, dL)
+    is_far = at >= n
+    assert np.isfinite(ref["img"]).all() and (ref["n_contrib"] > 0).any()
+    for name in ("img", "final_T", "n_contrib", "active"):
+        np.testing.assert_array_equal(got[name], ref[name], err_msg=name)
+    np.testing.assert_array_equal(got["grad2d"][~is_far], ref["grad2d"][~is_far])
+    np.testing.assert_array_equal(got["grad_rows"][~is_far], ref["grad_rows"][~is_far])
+    finite = is_far & np.isfinite(arrays[0]).all(1) & np.isfinite(arrays[1]).all(1)
+    assert (got["grad2d"][finite] == 0).all()
+
+
+def test_raster_distant_needles(torch_gpu):
+    """Footprints a pixel wide whose centres lie 1500 to 3000 px off the image along their
+    axis: the terms of sigma are 1e6 and more, sigma itself a few."""
+    width, height, n = 40, 33, 300
+    rng = np.random.default_rng(5)
+    uv, con, op, rgb = ordinary_pairs(rng, n, width, height)
+    th = rng.uniform(0, np.pi, n)
+    c, s = np.cos(th), np.sin(th)
+    s1, s2 = rng.uniform(900, 1200, n), 0.6
+    con = np.stack([(c / s1) ** 2 + (s / s2) ** 2, c * s * (s1 ** -2 - s2 ** -2), (s / s1) ** 2 + (c / s2) ** 2], 1)
+    con = con.astype(np.float32)
+    d = rng.uniform(1500, 3000, n) * rng.choice([-1, 1], n)
+    uv = (uv + np.stack([c, s], 1) * d[:, None]).astype(np.float32)
+    op[:] = rng.uniform(0.3, 0.985, n)
+    keep = con[:, 0].astype(np.float64) * con[:, 2] > con[:, 1].astype(np.float64) ** 2
+    uv, con, op, rgb = (a[keep] for a in (uv, con, op, rgb))
+    n = len(op)
+    assert n > 250
+    depth = rng.permutation(n).astype(np.float32) + 1
+    order = np.argsort(depth)
+    dL = rng.uniform(-1, 1, (3, height, width)).astype(np.float32)
+    img, fT, _, near, last = reference(uv, con, op, rgb, order, width, height, dL)
+    sure = near > 2e-5
+    dL *= sure
+    g = reference(uv, con, op, rgb, order, width, height, dL)[2]
+    got = blend_arrays(torch_gpu, uv, con, op, rgb, depth, width, height, dL)
+    assert sure.mean() > 0.97 and (last > 0).mean() > 0.5
+    # T after k pairs carries 2k roundings of 2^-24: 300 pairs, 3.6e-5
+    assert np.abs(got["img"] - img)[:, sure].max() <= 1e-4
+    np.testing.assert_array_equal(got["n_contrib"].reshape(height, width)[sure], last[sure])
+    bound = (4 * n + 200) * 2.0 ** -24 * (np.abs(g) + np.sqrt((g ** 2).mean(0)))
+    # (u, v)'s are differences of moments some thousand times their size
+    assert (np.abs(got["grad2d"] - g) <= bound + 1e-9)[:, 2:].all(), np.abs((got["grad2d"] - g) / bound).max(0)
