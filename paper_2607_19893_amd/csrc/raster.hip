@@ -59,7 +59,9 @@ struct __align__(16) Splat {
 // (kChecked) test sigma.  An indefinite pair, whose record carries -o, is skipped below
 // kSigmaNeg (a zero of sigma can come out as a tiny negative number).  A definite pair
 // further out has its negative sigmas, which are rounding, taken as 0, and those beyond
-// kSigmaFar, possibly past the fp32 range, as kSigmaFar, at which alpha is 0.  kCapped
+// kSigmaFar, possibly past the fp32 range, as kSigmaFar, at which alpha is 0.  A colour
+// that is not finite is kChecked too: those batches take it only where the pair is
+// included, since 0 times it is a NaN.  kCapped
 // marks an opacity above the 0.99 cap of alpha, at which the backward's derivatives of
 // alpha vanish.
 constexpr float kSigmaNeg = -1e-9f, kSigmaFar = 1e4f, kNearSize = 2.5e6f;
@@ -105,7 +107,8 @@ __device__ __forceinline__ uint32_t stage_pair(Splat* rec, float2 m, float4 co, 
     const float size = hA * mx * mx + fabsf(B) * mx * my + hC * my * my;
     const float lim = fmaf(1e-6f, size, cut);
     const bool definite = A > 0.0f && (double)A * C - (double)B * B > 0.0;
-    uint32_t mask = co.w > kAlphaMax ? kCapped : 0u;
+    const float no_colour = (rec->r - rec->r) + (rec->g - rec->g) + (rec->b - rec->b);     // 0, or a NaN
+    uint32_t mask = (co.w > kAlphaMax ? kCapped : 0u) | (no_colour == 0.0f ? 0u : kChecked);
     if (!definite || !(size <= kNearSize)) {
         if (isinf(u) || isinf(v) || isinf(A) || isinf(B) || isinf(C)) return 0u;
         mask = kChecked | kCapped;
@@ -310,11 +313,11 @@ __global__ void __launch_bounds__(GS_BLOCK, STATS ? 5 : 6) k_raster_fwd(
                         const bool go = !(Tn < kTMin);       // stop in front of a pair that would leave less
                         if (STATS && !go && T > 0.0f) term_at = bs - start + at / (uint32_t)sizeof(Splat) + 1u;
                         const float wgt = go ? al * T : 0.0f;
-                        c0 = fmaf(wgt, S.r, c0);
-                        c1 = fmaf(wgt, S.g, c1);
-                        c2 = fmaf(wgt, S.b, c2);
-                        T = go ? Tn : -fabsf(T);
                         ok = ok && go;
+                        c0 = fmaf(wgt, !CHECK || ok ? S.r : 0.0f, c0);
+                        c1 = fmaf(wgt, !CHECK || ok ? S.g : 0.0f, c1);
+                        c2 = fmaf(wgt, !CHECK || ok ? S.b : 0.0f, c2);
+                        T = go ? Tn : -fabsf(T);
                         lk = ok ? at : lk;
                         hit |= (ok_mask & __builtin_amdgcn_ballot_w64(go)) != 0ull ? 1u << i : 0u;
                         if (STATS && i0 + i < n_list) {
@@ -695,12 +698,14 @@ __global__ void __launch_bounds__(GS_BLOCK, 4) k_raster_bwd(
                         al = ok ? al : 0.0f;
                         const float inv_om = __builtin_amdgcn_rcpf(1.0f - al);
                         T = T * inv_om;
-                        const float gcol = gC0 * S.r + gC1 * S.g + gC2 * S.b;
+                        float gcol = gC0 * S.r + gC1 * S.g + gC2 * S.b;
+                        if (CHECK) gcol = ok ? gcol : 0.0f;
                         const float dalpha = gS * inv_om - T * gcol;        // -dL/dalpha
                         const float wgt = al * T;
                         gS = fmaf(wgt, gcol, gS);
-                        // the 0.99 cap stops d/d(opacity, sigma)
-                        const float ds = dalpha * (!CHECK || gv < kAlphaMax ? al : 0.0f);
+                        // the 0.99 cap stops d/d(opacity, sigma); a pixel whose gS is not finite passes
+                        // that on to the pairs it includes only
+                        const float ds = ok && (!CHECK || gv < kAlphaMax) ? dalpha * al : 0.0f;
                         const float dx = u - xj;
                         const float dsx = ds * dx;
                         *reinterpret_cast<float*>(my_sums + at) =

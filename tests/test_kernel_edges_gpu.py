@@ -417,3 +417,31 @@ def test_raster_distant_needles(torch_gpu):
     bound = (4 * n + 200) * 2.0 ** -24 * (np.abs(g) + np.sqrt((g ** 2).mean(0)))
     # (u, v)'s are differences of moments some thousand times their size
     assert (np.abs(got["grad2d"] - g) <= bound + 1e-9)[:, 2:].all(), np.abs((got["grad2d"] - g) / bound).max(0)
+
+
+def test_raster_colours_not_finite(torch_gpu):
+    """An infinite or NaN colour reaches the pixels that include its pair, and the gradients
+    of the pairs that share such a pixel, and nothing else."""
+    width, height, n = 61, 45, 330
+    rng = np.random.default_rng(8)
+    uv, con, op, rgb = ordinary_pairs(rng, n, width, height)
+    con *= np.float32(4.0)                                  # footprints of a few pixels
+    depth = rng.permutation(n).astype(np.float32) + 1
+    dL = rng.uniform(0.1, 1, (3, height, width)).astype(np.float32)
+    bad = rng.choice(n, 4, replace=False)
+    op[bad] = 0.3
+    run = lambda c, d: blend_arrays(torch_gpu, uv, con, op, c, depth, width, height, d)  # noqa: E731
+    black, white, col = rgb.copy(), rgb.copy(), rgb.copy()
+    black[bad], white[bad] = 0, 1
+    col[bad] = np.array([[np.inf, 0, 0], [0, np.nan, 0], [0, 0, -np.inf], [np.inf, np.nan, 1]], np.float32)
+    ref, got = run(black, dL), run(col, dL)
+    hit = (run(white, dL)["img"] != ref["img"]).any(0)      # pixels that include one of the four
+    assert 10 < hit.sum() < 0.3 * hit.size
+    for name in ("final_T", "n_contrib", "active"):
+        np.testing.assert_array_equal(got[name], ref[name], err_msg=name)
+    np.testing.assert_array_equal(got["img"][:, ~hit], ref["img"][:, ~hit])
+    assert not np.isfinite(got["img"][:, hit]).all(0).any()
+    clear = (run(black, dL * hit)["grad2d"] == 0).all(1)    # pairs that no such pixel includes
+    clear[bad] = False
+    assert clear.sum() > 50
+    np.testing.assert_array_equal(got["grad2d"][clear], ref["grad2d"][clear])
