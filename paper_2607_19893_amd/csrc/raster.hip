@@ -62,7 +62,7 @@ struct __align__(16) Splat {
 // kSigmaFar, possibly past the fp32 range, as kSigmaFar, at which alpha is 0.  A colour
 // that is not finite is kChecked too: those batches take it only where the pair is
 // included, since 0 times it is a NaN.  kCapped
-// marks an opacity above the 0.99 cap of alpha, at which the backward's derivatives of
+// marks an opacity from the 0.99 cap of alpha on, at which the backward's derivatives of
 // alpha vanish.
 constexpr float kSigmaNeg = -1e-9f, kSigmaFar = 1e4f, kNearSize = 2.5e6f;
 constexpr uint32_t kChecked = 1u << 16, kCapped = 1u << 17;
@@ -108,7 +108,7 @@ __device__ __forceinline__ uint32_t stage_pair(Splat* rec, float2 m, float4 co, 
     const float lim = fmaf(1e-6f, size, cut);
     const bool definite = A > 0.0f && (double)A * C - (double)B * B > 0.0;
     const float no_colour = (rec->r - rec->r) + (rec->g - rec->g) + (rec->b - rec->b);     // 0, or a NaN
-    uint32_t mask = (co.w > kAlphaMax ? kCapped : 0u) | (no_colour == 0.0f ? 0u : kChecked);
+    uint32_t mask = (co.w >= kAlphaMax ? kCapped : 0u) | (no_colour == 0.0f ? 0u : kChecked);
     if (!definite || !(size <= kNearSize)) {
         if (isinf(u) || isinf(v) || isinf(A) || isinf(B) || isinf(C)) return 0u;
         mask = kChecked | kCapped;

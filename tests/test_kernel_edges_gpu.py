@@ -445,3 +445,14 @@ def test_raster_colours_not_finite(torch_gpu):
     clear[bad] = False
     assert clear.sum() > 50
     np.testing.assert_array_equal(got["grad2d"][clear], ref["grad2d"][clear])
+
+
+def test_raster_bwd_opacity_at_the_cap(torch_gpu):
+    """o e^-sigma equal to the 0.99 cap of alpha stops the gradients of opacity and sigma."""
+    uv = np.array([[5.5, 9.5]], np.float32)
+    con, op = np.array([[1, 0, 1]], np.float32), np.array([0.99], np.float32)
+    dL = np.zeros((3, 16, 16), np.float32)
+    dL[:, 9, 5] = 1.0
+    got = blend_arrays(torch_gpu, uv, con, op, np.full((1, 3), 0.5, np.float32), np.ones(1, np.float32), 16, 16, dL)
+    np.testing.assert_array_equal(got["grad2d"][0, :6], 0)
+    np.testing.assert_array_equal(got["grad2d"][0, 6:], np.float32(0.99))
