@@ -501,11 +501,10 @@ constexpr int kSums = 8;              // floats a strip keeps per pair
 // with m = sum ds, m_x = sum ds dx, m_xy = sum ds dx dy and so on (the opacity
 // line because ds = -dL/dalpha * o e^-sigma below the 0.99 cap, and both are 0
 // at it).  Each 16-lane row of a wave renders an 8x2 strip of pixels and walks its
-// own list of the batch.  The strip's two pixel rows lie h = +-1/2 below and above
-// its middle, h^2 = 1/4, so eight sums hold all moments: of ds, ds dx, ds dx^2,
-// ds h, ds dx h and the three colour terms; with c the splat's offset from the
-// strip's middle row, m_y = c m - m_h, m_xy = c m_x - m_xh and
-// m_yy = c^2 m - 2 c m_h + m / 4.  A strip takes a pair at most once per batch, so
+// own list of the batch.  The pixels of one of the strip's two pixel rows share dy, so
+// eight sums hold all moments: of ds and ds dx over each pixel row, and of ds dx^2 and
+// the three colour terms over the strip.  dx and dy are differences of the fp32 centre and
+// the pixel centre's exact coordinate, rounded once.  A strip takes a pair at most once per batch, so
 // its sums go to the (strip, pair) record with plain LDS writes; after the walk
 // four threads per pair add the 16 strips' records in a fixed order.  A pair slot holds
 // (m_x, m_y, m_xx, m_xy, m_yy, m, colour); k_project_bwd expands it with the
@@ -523,36 +522,32 @@ constexpr int kSums = 8;              // floats a strip keeps per pair
 // 264 -> 213 us, 3M walk-through 151 -> 92, 200k ring at 720p 169 -> 132, 60k ring at
 // 651x433 143 -> 80, 10k box at 256x256 82 -> 46.
 
-// The sums of a..h over each 16-lane row, in 16 DPP additions: the halves of two
-// values are added into the two halves of one register, then the quarters of two
-// such registers into the quarters of one; two steps inside each quarter finish.
-// Returns quarter by quarter a, c, b, d in the even lanes and e, g, f, h in the odd
-// ones.  A DPP source must have been written at least two instructions earlier
+// Eight sums over each 16-lane row, in 12 DPP additions: of m and x over each half of the
+// row, of e..h over all of it.  The halves of two of e..h are added into the two halves of
+// one register; then the quarters of two registers (m and x as they are) into the
+// quarters of one, and two steps inside each quarter finish.  Returns quarter by quarter
+// m, x of the low half and m, x of the high half in the even lanes, and e, g, f, h in the
+// odd ones.  A DPP source must have been written at least two instructions earlier
 // (s_nop where the order does not see to it).
-__device__ __forceinline__ float row_sum8(float a, float b, float c, float d, float e, float f, float g, float h,
-                                          bool odd) {
+__device__ __forceinline__ float row_sum8(float m, float x, float e, float f, float g, float h, bool odd) {
     asm("s_nop 1\n\t"
-        "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %0, %4, %4 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
         "v_add_f32_dpp %1, %1, %1 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %1, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %1, %4, %4 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
         "v_add_f32_dpp %2, %2, %2 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %2, %6, %6 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-        "v_add_f32_dpp %3, %3, %3 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %3, %7, %7 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %2, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
         "v_add_f32_dpp %0, %0, %0 row_shl:4 row_mask:0xf bank_mask:0x5\n\t"
-        "v_add_f32_dpp %0, %1, %1 row_shr:4 row_mask:0xf bank_mask:0xa\n\t"
-        "v_add_f32_dpp %2, %2, %2 row_shl:4 row_mask:0xf bank_mask:0x5\n\t"
-        "v_add_f32_dpp %2, %3, %3 row_shr:4 row_mask:0xf bank_mask:0xa\n\t"
-        "s_nop 0\n\t"
+        "v_add_f32_dpp %0, %3, %3 row_shr:4 row_mask:0xf bank_mask:0xa\n\t"
+        "v_add_f32_dpp %1, %1, %1 row_shl:4 row_mask:0xf bank_mask:0x5\n\t"
+        "v_add_f32_dpp %1, %2, %2 row_shr:4 row_mask:0xf bank_mask:0xa\n\t"
         "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-        "v_add_f32_dpp %2, %2, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
         "s_nop 0\n\t"
+        "v_add_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
         "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-        "v_add_f32_dpp %2, %2, %2 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
-        : "+&v"(a), "+&v"(c), "+&v"(e), "+&v"(g)
-        : "v"(b), "v"(d), "v"(f), "v"(h));
-    return odd ? e : a;
+        "s_nop 0\n\t"
+        "v_add_f32_dpp %1, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+        : "+&v"(m), "+&v"(e), "+&v"(g)
+        : "v"(x), "v"(f), "v"(h));
+    return odd ? e : m;
 }
 
 __device__ __forceinline__ float quad_add(float v) {
@@ -569,7 +564,7 @@ __global__ void __launch_bounds__(GS_BLOCK, 4) k_raster_bwd(
     // record and sums kBwdBatch belong to a pair that blends nothing: it pads the lists
     __shared__ Splat L[kBwdBatch + 1];
     __shared__ __align__(16) float s_sum[4 * kStrips][kBwdBatch + 1][kSums];
-    __shared__ float s_u[kBwdBatch + 1], s_v[kBwdBatch];      // splat centres, relative to the tile's
+    __shared__ float s_u[kBwdBatch + 1], s_v[kBwdBatch];      // splat centres
     __shared__ __align__(4) uint16_t s_list[4 * kStrips][kBwdBatch + kBwdPad];   // per strip: byte offsets of its pairs' sums
     __shared__ uint32_t s_emit[kBwdBatch];
     __shared__ uint32_t s_max[4];
@@ -613,7 +608,7 @@ __global__ void __launch_bounds__(GS_BLOCK, 4) k_raster_bwd(
     if (tid < 4 * kStrips * kBwdPad) s_list[tid / kBwdPad][kBwdBatch + tid % kBwdPad] = (uint16_t)(kBwdBatch * kStep);
     __syncthreads();
     const uint32_t maxlast = max(max(s_max[0], s_max[1]), max(s_max[2], s_max[3]));
-    const float xj = (float)quad_x(tid) - 7.5f, h = (lane & 8) ? 0.5f : -0.5f;
+    const float xj = (float)px + 0.5f;      // (exact: an image side has at most 16 bits)
     // where this lane stores its sum: row_sum8 leaves sum (bank, odd) in every lane of a bank's parity
     const bool odd = (lane & 1) != 0;
     const int bank = (lane >> 2) & 3;
@@ -648,8 +643,8 @@ __global__ void __launch_bounds__(GS_BLOCK, 4) k_raster_bwd(
             if (w == b) {
                 uint32_t mask = 0u;
                 if ((uint32_t)lane < cnt && pos < maxlast) mask = stage_pair<2>(&L[lane], m, co, cr, xc, yc);
-                s_u[lane] = (float)((double)m.x - xc);
-                s_v[lane] = (float)((double)m.y - yc);
+                s_u[lane] = m.x;
+                s_v[lane] = mask ? m.y : 0.0f;      // (of a pair no pixel takes it may be infinite)
                 s_mask[lane] = (uint16_t)mask;
                 s_emit[lane] = emit;
                 const uint64_t sp = __ballot((mask & (kChecked | kCapped)) != 0u);
@@ -709,7 +704,7 @@ __global__ void __launch_bounds__(GS_BLOCK, 4) k_raster_bwd(
                         const float dx = u - xj;
                         const float dsx = ds * dx;
                         *reinterpret_cast<float*>(my_sums + at) =
-                            row_sum8(ds, dsx * dx, dsx, ds * h, dsx * h, wgt * gC1, wgt * gC0, wgt * gC2, odd);
+                            row_sum8(ds, dsx, dsx * dx, wgt * gC1, wgt * gC0, wgt * gC2, odd);
                     }
                 }
             };
@@ -733,17 +728,17 @@ __global__ void __launch_bounds__(GS_BLOCK, 4) k_raster_bwd(
                     const float4 a1 = *reinterpret_cast<const float4*>(&s_sum[sl][k][4]);
                     const float4 b0 = *reinterpret_cast<const float4*>(&s_sum[sl + kStrips][k][0]);
                     const float4 b1 = *reinterpret_cast<const float4*>(&s_sum[sl + kStrips][k][4]);
-                    // as stored: a, c, b, d = m, m_x, m_xx, m_h; e, g, f, h = m_xh, colours
-                    const float sm = a0.x + b0.x, sx = a0.y + b0.y, sxx = a0.z + b0.z, sh = a0.w + b0.w,
-                                sxh = a1.x + b1.x;
-                    const float c = v - (2.0f * (float)row - 7.0f);
-                    const float my = fmaf(c, sm, -sh);
-                    acc[0] += sx;
-                    acc[1] += my;
-                    acc[2] += sxx;
-                    acc[3] += fmaf(c, sx, -sxh);
-                    acc[4] += fmaf(c, my - sh, 0.25f * sm);
-                    acc[5] += sm;
+                    // as stored: m, m_x of the upper and of the lower pixel row; m_xx and the colours
+                    const float m0 = a0.x + b0.x, x0 = a0.y + b0.y, m1 = a0.z + b0.z, x1 = a0.w + b0.w;
+                    const float y = (float)(ty * GS_TILE + 2 * (int)row) + 0.5f;
+                    const float dy0 = v - y, dy1 = v - (y + 1.0f);
+                    const float y0 = dy0 * m0, y1 = dy1 * m1;
+                    acc[0] += x0 + x1;
+                    acc[1] += y0 + y1;
+                    acc[2] += a1.x + b1.x;
+                    acc[3] += fmaf(dy0, x0, dy1 * x1);
+                    acc[4] += fmaf(dy0, y0, dy1 * y1);
+                    acc[5] += m0 + m1;
                     acc[6] += a1.y + b1.y;
                     acc[7] += a1.z + b1.z;
                     acc[8] += a1.w + b1.w;

@@ -456,3 +456,30 @@ def test_raster_bwd_opacity_at_the_cap(torch_gpu):
     got = blend_arrays(torch_gpu, uv, con, op, np.full((1, 3), 0.5, np.float32), np.ones(1, np.float32), 16, 16, dL)
     np.testing.assert_array_equal(got["grad2d"][0, :6], 0)
     np.testing.assert_array_equal(got["grad2d"][0, 6:], np.float32(0.99))
+
+
+def test_raster_bwd_small_offsets(torch_gpu):
+    """Centres 2e-4 to 5e-3 px off a pixel centre, one included pixel each: the moments keep
+    the offsets' own precision, not that of their distance to a strip or a tile."""
+    width, height = 48, 40
+    rng = np.random.default_rng(4)
+    px, py = [a.reshape(-1) for a in np.meshgrid(np.arange(0, width, 3), np.arange(0, height))]
+    n = px.size
+    off = rng.uniform(2e-4, 5e-3, (n, 2)) * rng.choice([-1, 1], (n, 2))
+    uv = (np.stack([px, py], 1) + 0.5 + off).astype(np.float32)
+    con = np.tile(np.array([4000, 900, 4800], np.float32), (n, 1))
+    op = rng.uniform(0.1, 0.9, n).astype(np.float32)
+    rgb = rng.uniform(0.2, 1, (n, 3)).astype(np.float32)
+    dL = rng.uniform(0.2, 1, (3, height, width)).astype(np.float32)
+    got = blend_arrays(torch_gpu, uv, con, op, rgb, rng.permutation(n).astype(np.float32) + 1, width, height, dL)
+    d = uv.astype(np.float64) - np.stack([px, py], 1) - 0.5
+    A, B, C = con.astype(np.float64).T
+    sigma = 0.5 * (A * d[:, 0] ** 2 + C * d[:, 1] ** 2) + B * d[:, 0] * d[:, 1]
+    ds = -(dL[:, py, px].T.astype(np.float64) * rgb).sum(1) * op * np.exp(-sigma)
+    x, y = d.T
+    ref = ds[:, None] * np.stack([A * x + B * y, B * x + C * y, x * x / 2, x * y, y * y / 2], 1)
+    mag = np.abs(ds)[:, None] * np.stack([abs(A * x) + abs(B * y), abs(B * x) + abs(C * y), x * x / 2, abs(x * y),
+                                          y * y / 2], 1)
+    # alpha, T and dL/dalpha carry about ten roundings, the offsets and products four more
+    assert (np.abs(got["grad2d"][:, :5] - ref) <= 24 * 2.0 ** -24 * mag).all(), \
+        (np.abs(got["grad2d"][:, :5] - ref) / mag).max(0) * 2 ** 24
