@@ -54,25 +54,22 @@ struct __align__(16) Splat {
 //   size = A/2 x^2 + |B| x y + C/2 y^2,  (x, y) = (|u| + 7.5, |v| + 7.5),
 // (u, v) the centre from the tile's: nine roundings on the way to the coefficients
 // and five of the evaluation, each of a sum of terms that lie within size.  Up to
-// kNearSize that is below 5e-9: a definite pair's sigma neither overflows nor makes
-// exp(-sigma) round above 1, and needs no test.  Batches that hold another pair
+// kNearSize that is below 5e-9: a definite pair's sigma neither overflows nor turns
+// visibly negative, and needs no test.  Batches that hold another pair
 // (kChecked) test sigma.  An indefinite pair, whose record carries -o, is skipped below
 // kSigmaNeg (a zero of sigma can come out as a tiny negative number).  A definite pair
 // further out has its negative sigmas, which are rounding, taken as 0, and those beyond
 // kSigmaFar, possibly past the fp32 range, as kSigmaFar, at which alpha is 0.  A colour
 // that is not finite is kChecked too: those batches take it only where the pair is
-// included, since 0 times it is a NaN.  kCapped
-// marks an opacity from the 0.99 cap of alpha on, at which the backward's derivatives of
-// alpha vanish.
+// included, since 0 times it is a NaN.
 constexpr float kSigmaNeg = -1e-9f, kSigmaFar = 1e4f, kNearSize = 2.5e6f;
-constexpr uint32_t kChecked = 1u << 16, kCapped = 1u << 17;
+constexpr uint32_t kChecked = 1u << 16;
 
 // Fills rec from a pair's mean, conic and colour, relative to the tile centre
 // (xc, yc), and returns the tile's blocks of 8 x BH pixels that hold a pixel centre
 // with sigma <= cut = ln(255 o) + kCutMargin: a block that is left out has no pixel
 // at or above alpha = 1/255.  Bit b is the block of wave b / (8 / BH) (quadrant
-// (w & 1, w >> 1)), counted downwards inside the quadrant; kChecked and kCapped
-// come on top.
+// (w & 1, w >> 1)), counted downwards inside the quadrant; kChecked comes on top.
 //
 // sigma's minimum over a rectangle lies at its centre if that is inside, else on
 // the vertical or horizontal edge line nearest to the centre: along each of the
@@ -108,10 +105,10 @@ __device__ __forceinline__ uint32_t stage_pair(Splat* rec, float2 m, float4 co, 
     const float lim = fmaf(1e-6f, size, cut);
     const bool definite = A > 0.0f && (double)A * C - (double)B * B > 0.0;
     const float no_colour = (rec->r - rec->r) + (rec->g - rec->g) + (rec->b - rec->b);     // 0, or a NaN
-    uint32_t mask = (co.w >= kAlphaMax ? kCapped : 0u) | (no_colour == 0.0f ? 0u : kChecked);
+    uint32_t mask = no_colour == 0.0f ? 0u : kChecked;
     if (!definite || !(size <= kNearSize)) {
         if (isinf(u) || isinf(v) || isinf(A) || isinf(B) || isinf(C)) return 0u;
-        mask = kChecked | kCapped;
+        mask = kChecked;
         if (!definite) {
             const bool nan = u != u || v != v || (A > 0.0f && (B != B || C != C));
             rec->o = -co.w;
@@ -568,7 +565,7 @@ __global__ void __launch_bounds__(GS_BLOCK, 4) k_raster_bwd(
     __shared__ __align__(4) uint16_t s_list[4 * kStrips][kBwdBatch + kBwdPad];   // per strip: byte offsets of its pairs' sums
     __shared__ uint32_t s_emit[kBwdBatch];
     __shared__ uint32_t s_max[4];
-    __shared__ uint32_t s_special;
+    __shared__ uint32_t s_checked;
     __shared__ uint16_t s_mask[kBwdBatch];
     constexpr uint32_t kStep = kSums * sizeof(float);          // a list entry is pair k's k * kStep
     static_assert(sizeof(Splat) == 2 * kStep, "a record lies at twice its sums' offset");
@@ -647,8 +644,8 @@ __global__ void __launch_bounds__(GS_BLOCK, 4) k_raster_bwd(
                 s_v[lane] = mask ? m.y : 0.0f;      // (of a pair no pixel takes it may be infinite)
                 s_mask[lane] = (uint16_t)mask;
                 s_emit[lane] = emit;
-                const uint64_t sp = __ballot((mask & (kChecked | kCapped)) != 0u);
-                if (lane == 0) s_special = sp != 0ull ? 1u : 0u;
+                const uint64_t check = __ballot((mask & kChecked) != 0u);
+                if (lane == 0) s_checked = check != 0ull ? 1u : 0u;
             }
             __syncthreads();
             // the strips' lists, back to front and filled up with the pad; pairs a strip does not take leave zero sums
@@ -678,37 +675,46 @@ __global__ void __launch_bounds__(GS_BLOCK, 4) k_raster_bwd(
                 constexpr bool CHECK = decltype(checked)::value;
                 for (uint32_t i0 = 0; i0 < n_list; i0 += kBwdPad) {
                     const uint32_t at2 = *reinterpret_cast<const uint32_t*>(list + i0);
+                    // the pairs' records and footprints side by side, then the chain through T and gS
+                    float capped[kBwdPad], u[kBwdPad], c0[kBwdPad], c1[kBwdPad], c2[kBwdPad];
+                    bool on[kBwdPad];
 #pragma unroll
                     for (int i = 0; i < kBwdPad; ++i) {
                         const uint32_t at = i ? at2 >> 16 : at2 & 0xFFFFu;
                         const Splat& S = *reinterpret_cast<const Splat*>(reinterpret_cast<const char*>(L) + 2 * at);
-                        const float u = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(s_u) + at / kSums);
+                        u[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(s_u) + at / kSums);
+                        c0[i] = S.r;
+                        c1[i] = S.g;
+                        c2[i] = S.b;
                         float sigma = P.eval(S), o = S.o;
-                        const bool on = !CHECK || check_sigma(S, sigma, o);
-                        const float gv = o * exp_neg(sigma);
-                        float al = CHECK ? fminf(kAlphaMax, gv) : gv;
+                        on[i] = !CHECK || check_sigma(S, sigma, o);
+                        capped[i] = fminf(kAlphaMax, o * exp_neg(sigma));
+                    }
+#pragma unroll
+                    for (int i = 0; i < kBwdPad; ++i) {
+                        const uint32_t at = i ? at2 >> 16 : at2 & 0xFFFFu;
                         // a lane without the pair takes alpha = 0: its T stays, its weight and ds are 0
-                        bool ok = (at < last_b) & !(al < kAlphaMin);
-                        if (CHECK) ok = ok & on;
-                        al = ok ? al : 0.0f;
+                        bool ok = (at < last_b) & !(capped[i] < kAlphaMin);
+                        if (CHECK) ok = ok & on[i];
+                        const float al = ok ? capped[i] : 0.0f;
                         const float inv_om = __builtin_amdgcn_rcpf(1.0f - al);
                         T = T * inv_om;
-                        float gcol = gC0 * S.r + gC1 * S.g + gC2 * S.b;
+                        float gcol = gC0 * c0[i] + gC1 * c1[i] + gC2 * c2[i];
                         if (CHECK) gcol = ok ? gcol : 0.0f;
                         const float dalpha = gS * inv_om - T * gcol;        // -dL/dalpha
                         const float wgt = al * T;
                         gS = fmaf(wgt, gcol, gS);
                         // the 0.99 cap stops d/d(opacity, sigma); a pixel whose gS is not finite passes
                         // that on to the pairs it includes only
-                        const float ds = ok && (!CHECK || gv < kAlphaMax) ? dalpha * al : 0.0f;
-                        const float dx = u - xj;
+                        const float ds = ok & (capped[i] < kAlphaMax) ? dalpha * al : 0.0f;
+                        const float dx = u[i] - xj;
                         const float dsx = ds * dx;
                         *reinterpret_cast<float*>(my_sums + at) =
                             row_sum8(ds, dsx, dsx * dx, wgt * gC1, wgt * gC0, wgt * gC2, odd);
                     }
                 }
             };
-            if (s_special)
+            if (s_checked)
                 walk(std::true_type{});
             else
                 walk(std::false_type{});
@@ -716,7 +722,9 @@ __global__ void __launch_bounds__(GS_BLOCK, 4) k_raster_bwd(
             // four threads per pair, two strips' rows of the tile each (both quadrants
             // beside each other share the rows); the slot is the pair's emission
             // position: a primitive's pairs end up side by side for k_slot_sum
-            const uint32_t k = (uint32_t)tid >> 2, part = (uint32_t)tid & 3u;
+            const uint32_t k = (uint32_t)tid >> 2;
+            uint32_t part = (uint32_t)tid & 3u;
+            loaded(part);       // (formed here and not kept through the walk, whose two pairs need the registers)
             if (k < cnt) {
                 float acc[kG] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
                 const float v = s_v[k];
