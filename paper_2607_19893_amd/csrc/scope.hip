@@ -286,23 +286,29 @@ __device__ __forceinline__ float wave_max_f32(float v) {
     return v;
 }
 
-// Words of a gate block: every wave loads all 64, one per lane, and takes a quarter of
-// the 32 passes over their 2048 ids.  The loads of a wave's passes are in flight
-// together (a wave with 32 passes of its own, four in flight: 12.4 us at 3M ids; this: 7.4 us).
-constexpr int kGateWords = GS_WAVE;
-constexpr int kGatePasses = kGateWords / 2 / (GS_BLOCK / GS_WAVE);
+// A gate block covers the 256 words (8192 ids) that a workgroup's partial record stands
+// for, with 16 waves: four share 64 of the words, each wave loading them, one per lane, and
+// taking a quarter of the 32 passes over their 2048 ids.  The loads of a wave's passes are
+// in flight together.  Measured at 3M ids: a wave with 32 passes of its own, four in
+// flight, 12.4 us; records of 2048 ids by four waves 7.0, and 4.2 in the decision over
+// four times as many; this 7.7 and 3.3.
+constexpr int kGateBlock = 1024;
+constexpr int kGateWaves = kGateBlock / GS_WAVE, kGateQuads = kWordsPerBlock / GS_WAVE;
+constexpr int kGatePasses = GS_WAVE / 2 / (kGateWaves / kGateQuads);
 
-__global__ void __launch_bounds__(GS_BLOCK) k_gate_partial(GateIn in, int32_t n, uint32_t nwords,
-                                                           GatePartial* __restrict__ partial) {
-    __shared__ double s_sum[4];
-    __shared__ float s_max[4];
-    __shared__ uint32_t s_second[4];
+__global__ void __launch_bounds__(kGateBlock) k_gate_partial(GateIn in, int32_t n, uint32_t nwords,
+                                                             GatePartial* __restrict__ partial) {
+    __shared__ double s_sum[kGateWaves];
+    __shared__ float s_max[kGateWaves];
+    __shared__ uint32_t s_second[kGateWaves];
+    __shared__ uint4 s_cnt[kGateQuads];
     const int lane = lane_id(), wv = threadIdx.x / GS_WAVE;
-    const uint32_t w0 = blockIdx.x * kGateWords, w = w0 + (uint32_t)lane;
+    const int quad = wv / (kGateWaves / kGateQuads), part = wv % (kGateWaves / kGateQuads);
+    const uint32_t w0 = blockIdx.x * kWordsPerBlock + (uint32_t)quad * GS_WAVE, w = w0 + (uint32_t)lane;
     const uint32_t mask = tail_mask(w, nwords, n);
     const uint32_t d = load_word(in.D, w, nwords, mask);
     const uint32_t ca = load_word(in.CA, w, nwords, mask);
-    // pass j covers ids [64 j, 64 j + 64) of the block's, lane l taking id 64 j + l,
+    // pass j covers ids [64 j, 64 j + 64) of the 64 words', lane l taking id 64 j + l,
     // whose bit sits in the word of lane 2 j + (l >> 5)
     float gv[kGatePasses];
     uint32_t sk[kGatePasses];
@@ -310,12 +316,19 @@ __global__ void __launch_bounds__(GS_BLOCK) k_gate_partial(GateIn in, int32_t n,
     const uint32_t bit = 1u << (lane & 31);
 #pragma unroll
     for (int j = 0; j < kGatePasses; ++j) {
-        const int src = 2 * (wv * kGatePasses + j) + (lane >> 5);
+        const int src = 2 * (part * kGatePasses + j) + (lane >> 5);
         act[j] = ((uint32_t)__shfl((int)ca, src, GS_WAVE) & bit) != 0u;
         del[j] = ((uint32_t)__shfl((int)d, src, GS_WAVE) & bit) != 0u;
         const uint32_t id = ((w0 + (uint32_t)src) << 5) + (uint32_t)(lane & 31);
         gv[j] = act[j] || del[j] ? in.g[id] : 0.0f;
         sk[j] = del[j] && in.skip != nullptr ? in.skip[id] : 0u;
+    }
+    if (part == 0) {
+        const uint32_t rb = load_word(in.RB, w, nwords, mask);
+        const uint32_t ev = load_word(in.E, w, nwords, mask);
+        const uint4 c = make_uint4(wave_sum_u32(__popc(rb)), wave_sum_u32(__popc(d)), wave_sum_u32(__popc(ca)),
+                                   wave_sum_u32(__popc(d & ~ev)));
+        if (lane == 0) s_cnt[quad] = c;
     }
     double sum = 0.0;
     float mx = 0.0f;
@@ -335,20 +348,21 @@ __global__ void __launch_bounds__(GS_BLOCK) k_gate_partial(GateIn in, int32_t n,
         s_second[wv] = second;
     }
     __syncthreads();
-    if (wv != 0) return;
-    const uint32_t rb = load_word(in.RB, w, nwords, mask);
-    const uint32_t ev = load_word(in.E, w, nwords, mask);
-    GatePartial p;
-    p.n_read = wave_sum_u32(__popc(rb));
-    p.n_delayed = wave_sum_u32(__popc(d));
-    p.n_active = wave_sum_u32(__popc(ca));
-    p.n_missing = wave_sum_u32(__popc(d & ~ev));
-    p.n_second = (s_second[0] + s_second[1]) + (s_second[2] + s_second[3]);
-    p.max_bits = __float_as_uint(fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3])));
-    p.pad0 = p.pad1 = 0;
-    p.sum_g = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
-    p.pad2 = 0.0;
-    if (lane == 0) partial[blockIdx.x] = p;
+    if (threadIdx.x != 0) return;
+    GatePartial p = {};
+    for (int q = 0; q < kGateQuads; ++q) {
+        p.n_read += s_cnt[q].x;
+        p.n_delayed += s_cnt[q].y;
+        p.n_active += s_cnt[q].z;
+        p.n_missing += s_cnt[q].w;
+    }
+    for (int i = 0; i < kGateWaves; ++i) {
+        p.n_second += s_second[i];
+        p.sum_g += s_sum[i];
+        mx = fmaxf(mx, s_max[i]);
+    }
+    p.max_bits = __float_as_uint(mx);
+    partial[blockIdx.x] = p;
 }
 
 // One workgroup: fixed-order reduction of the partials (four records a thread in
@@ -450,8 +464,7 @@ __global__ void __launch_bounds__(GS_BLOCK) k_gate_mark(const uint32_t* __restri
 }  // namespace
 
 size_t scope_ws_bytes(int32_t n) {
-    // the gate's records; the hazard counts (16 bytes per 256 words) are fewer
-    const uint32_t nb = div_up(div_up((uint64_t)(n > 0 ? n : 0), 32), kGateWords);
+    const uint32_t nb = div_up(div_up((uint64_t)(n > 0 ? n : 0), 32), kWordsPerBlock);
     return align256(sizeof(GatePartial) * (size_t)(nb + 1));
 }
 
@@ -516,19 +529,19 @@ hipError_t launch_scope_conflicts(const uint32_t* RA, const uint32_t* WA, const 
 hipError_t launch_admission_gate(const uint32_t* RB, const uint32_t* D, const gs_gate_args& a, int32_t n,
                                  gs_gate_result* result, void* ws, hipStream_t st) {
     const uint32_t nwords = div_up((uint64_t)(n > 0 ? n : 0), 32);
-    const uint32_t nb = div_up(nwords, kGateWords);
+    const uint32_t nb = div_up(nwords, kWordsPerBlock);
     GatePartial* partial = static_cast<GatePartial*>(ws);
     const GateIn in{RB, D, a.active, a.evidence ? a.evidence : a.active, a.g, a.skip, a.producer_version};
     if (nb > 0) {
-        hipLaunchKernelGGL(k_gate_partial, dim3(nb), dim3(GS_BLOCK), 0, st, in, n, nwords, partial);
+        hipLaunchKernelGGL(k_gate_partial, dim3(nb), dim3(kGateBlock), 0, st, in, n, nwords, partial);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(k_gate_decide, dim3(1), dim3(GS_BLOCK), 0, st, partial, nb, a.tau, result);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.skip == nullptr || nb == 0) return e;
-    hipLaunchKernelGGL(k_gate_mark, dim3(div_up(nwords, kWordsPerBlock)), dim3(GS_BLOCK), 0, st, D, n, nwords, result,
-                       a.producer_version, a.skip);
+    hipLaunchKernelGGL(k_gate_mark, dim3(nb), dim3(GS_BLOCK), 0, st, D, n, nwords, result, a.producer_version,
+                       a.skip);
     return hipGetLastError();
 }
 

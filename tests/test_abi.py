@@ -174,6 +174,9 @@ def test_workspace_sizes_monotone(gs):
     assert gs.gs_workspace_bytes(gs.GS_WS_RASTER_BWD, 1000, 100) >= 12 * 4 * 100
     assert gs.gs_workspace_bytes(gs.GS_WS_RASTER_BWD, 0, 5000) > gs.gs_workspace_bytes(gs.GS_WS_RASTER_BWD, 0, 100)
     assert gs.gs_workspace_bytes(99, 10, 10) == 0
+    # the scope calls' workspace: one 48-byte record per 8192 ids and one more
+    for n in (0, 1, 8192, 8193, 1 << 20, 10_000_000):
+        assert gs.gs_workspace_bytes(gs.GS_WS_SCOPE, n) == (48 * (-(-n // 8192) + 1) + 255) // 256 * 256
     assert 0 < gs.gs_workspace_bytes(gs.GS_WS_SCOPE, 100) <= gs.gs_workspace_bytes(gs.GS_WS_SCOPE, 10_000_000)
 
 

@@ -211,6 +211,30 @@ def test_admission_gate(n, torch_gpu, gs, orc):
                     orc.GATE_WAIT_MISSING, orc.GATE_WAIT_GRADIENT}
 
 
+# around a wave's 2048 ids and a record's 8192; 208 records (a round of one per thread is not
+# full), 1025 and 1465 (a second round, whose reads past the last record must count nothing)
+@pytest.mark.parametrize("n", [2047, 2048, 2049, 8191, 8193, 1_700_003, 1025 * 8192 - 8191, 12_000_017])
+def test_admission_gate_records(n, torch_gpu, gs, orc):
+    """Delayed ids in the last record too, one of them with the largest magnitude and one
+    named by another producer, among |g| that the mean and the counts all depend on."""
+    rng = np.random.default_rng(n)
+    RB = np.flatnonzero(rng.random(n) < 0.5)
+    CA = np.union1d(np.flatnonzero(rng.random(n) < 0.3), [n - 2, n - 1])
+    D = np.union1d(CA[rng.random(CA.size) < 0.02], [n - 2, n - 1])
+    RB = np.union1d(RB, D)
+    g = (rng.random(n) * 0.5).astype(np.float32)
+    g[n - 1] = 0.75
+    skip = np.zeros(n, np.uint32)
+    skip[D[::3]] = 7
+    skip[n - 2] = 5
+    for tau, version, evidence in ((1.0, 7, None), (1.0, 5, CA[CA != n - 1]), (0.2, 9, None)):
+        r, s = gate_on_gpu(torch_gpu, gs, n, RB, D, CA, g, tau, evidence=evidence, skip=skip, version=version)
+        ref, s_ref = orc.admission_gate(RB, D, CA, g, tau, evidence=evidence, skip=skip, producer_version=version)
+        assert_gate_equal(r, ref, (tau, version))
+        assert r.max_g == np.float32(0.75)
+        np.testing.assert_array_equal(s, s_ref)
+
+
 def test_admission_gate_metadata(torch_gpu, gs, orc):
     """Publication metadata: an admitted delayed set records the producer
     version; a second producer on a marked primitive waits; a refused gate
