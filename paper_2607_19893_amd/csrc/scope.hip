@@ -113,6 +113,12 @@ struct Hazards {
     uint32_t waw, raw, war, rb;
 };
 
+// A block's counts of them, four words of the workspace at any word's address (one
+// 16-byte load all the same).
+struct HazardCounts {
+    uint32_t waw, raw, war, rb;
+};
+
 __device__ __forceinline__ Hazards hazard_words(const ScopeIn& s, uint32_t w, uint32_t nwords, int32_t n) {
     const uint32_t mask = tail_mask(w, nwords, n);
     const uint32_t ra = load_word(s.RA, w, nwords, mask), wa = load_word(s.WA, w, nwords, mask);
@@ -199,44 +205,43 @@ __global__ void __launch_bounds__(GS_BLOCK) k_hazard_scatter(ScopeIn s, int32_t 
                                                              uint32_t* __restrict__ war_idx,
                                                              uint32_t* __restrict__ counts) {
     __shared__ uint32_t scratch[4];
-    __shared__ uint4 s_before[GS_BLOCK / GS_WAVE];
-    const uint4* records = reinterpret_cast<const uint4*>(partial);
-    uint4 before;
+    __shared__ HazardCounts s_before[GS_BLOCK / GS_WAVE];
+    const HazardCounts* records = reinterpret_cast<const HazardCounts*>(partial);
+    HazardCounts before = {0u, 0u, 0u, 0u};
     if (SUM) {
-        uint4 acc = make_uint4(0u, 0u, 0u, 0u);
+        HazardCounts acc = {0u, 0u, 0u, 0u};
         for (uint32_t i = threadIdx.x; i < blockIdx.x; i += 4 * GS_BLOCK) {
-            uint4 v[4];
+            HazardCounts v[4];
 #pragma unroll
             for (uint32_t j = 0; j < 4; ++j)
-                v[j] = i + j * GS_BLOCK < blockIdx.x ? records[i + j * GS_BLOCK] : make_uint4(0u, 0u, 0u, 0u);
+                v[j] = i + j * GS_BLOCK < blockIdx.x ? records[i + j * GS_BLOCK] : HazardCounts{0u, 0u, 0u, 0u};
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                acc.x += v[j].x;
-                acc.y += v[j].y;
-                acc.z += v[j].z;
-                acc.w += v[j].w;
+                acc.waw += v[j].waw;
+                acc.raw += v[j].raw;
+                acc.war += v[j].war;
+                acc.rb += v[j].rb;
             }
         }
-        acc.x = wave_sum_u32(acc.x);
-        acc.y = wave_sum_u32(acc.y);
-        acc.z = wave_sum_u32(acc.z);
-        acc.w = wave_sum_u32(acc.w);
+        acc.waw = wave_sum_u32(acc.waw);
+        acc.raw = wave_sum_u32(acc.raw);
+        acc.war = wave_sum_u32(acc.war);
+        acc.rb = wave_sum_u32(acc.rb);
         if (lane_id() == 0) s_before[threadIdx.x / GS_WAVE] = acc;
         __syncthreads();
-        before = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
         for (int j = 0; j < GS_BLOCK / GS_WAVE; ++j) {
-            before.x += s_before[j].x;
-            before.y += s_before[j].y;
-            before.z += s_before[j].z;
-            before.w += s_before[j].w;
+            before.waw += s_before[j].waw;
+            before.raw += s_before[j].raw;
+            before.war += s_before[j].war;
+            before.rb += s_before[j].rb;
         }
         if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-            const uint4 own = records[blockIdx.x];
-            counts[0] = before.x + own.x;
-            counts[1] = before.y + own.y;
-            counts[2] = before.z + own.z;
-            counts[3] = before.w + own.w;
+            const HazardCounts own = records[blockIdx.x];
+            counts[0] = before.waw + own.waw;
+            counts[1] = before.raw + own.raw;
+            counts[2] = before.war + own.war;
+            counts[3] = before.rb + own.rb;
         }
     } else {
         before = records[blockIdx.x];
@@ -244,9 +249,9 @@ __global__ void __launch_bounds__(GS_BLOCK) k_hazard_scatter(ScopeIn s, int32_t 
     const uint32_t w = blockIdx.x * kWordsPerBlock + threadIdx.x;
     const Hazards h = hazard_words(s, w, nwords, n);
     uint32_t tot;
-    const uint32_t p0 = block_excl_scan(__popc(h.waw), scratch, &tot) + before.x;
-    const uint32_t p1 = block_excl_scan(__popc(h.raw), scratch, &tot) + before.y;
-    const uint32_t p2 = block_excl_scan(__popc(h.war), scratch, &tot) + before.z;
+    const uint32_t p0 = block_excl_scan(__popc(h.waw), scratch, &tot) + before.waw;
+    const uint32_t p1 = block_excl_scan(__popc(h.raw), scratch, &tot) + before.raw;
+    const uint32_t p2 = block_excl_scan(__popc(h.war), scratch, &tot) + before.war;
     const uint32_t base = w << 5;
     if (waw_idx) scatter_bits(h.waw, base, p0, waw_idx);
     if (raw_idx) scatter_bits(h.raw, base, p1, raw_idx);

@@ -295,7 +295,8 @@ def test_hazard_lists_over_many_blocks(n, torch_gpu, gs):
     out = [torch.zeros(gs.scope_words(n), dtype=torch.int32, device="cuda") for _ in range(3)]
     ids = [torch.zeros(60000, dtype=torch.int32, device="cuda") for _ in range(3)]
     counts = torch.zeros(4, dtype=torch.int32, device="cuda")
-    ws = torch.zeros(gs.gs_workspace_bytes(gs.GS_WS_SCOPE, n), dtype=torch.uint8, device="cuda")
+    # a workspace at any word's address will do
+    ws = torch.zeros(gs.gs_workspace_bytes(gs.GS_WS_SCOPE, n) + 4, dtype=torch.uint8, device="cuda")[4:]
     gs.gs_scope_conflicts(*s, n, *out, *ids, counts, ws)
     ref = [np.intersect1d(WB, WA), np.intersect1d(np.setdiff1d(RB, WB), WA),
            np.setdiff1d(np.intersect1d(WB, RA), WA)]
