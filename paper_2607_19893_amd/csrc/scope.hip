@@ -190,10 +190,13 @@ __device__ __forceinline__ void scatter_bits(uint32_t word, uint32_t base_id, ui
 }
 
 // Blocks up to which the scatter adds up the counts of the blocks before it itself (a
-// few 16-byte loads a thread) instead of after k_hazard_offsets: the one-workgroup
-// launch took 5.6 us of 17 at 367 blocks.  Beyond, the loads (which grow with the
-// square of the blocks) outweigh it.
-constexpr uint32_t kSumBlocks = 4096;
+// few 16-byte loads a thread) instead of after k_hazard_offsets.  Its loads grow with the
+// square of the blocks, that one-workgroup launch with their number, and the two meet
+// between 32,768 and 49,152 blocks.  Measured, this scatter against that launch and its
+// scatter: 367 blocks (3M ids) 7.0 us against 5.1 + 6.4, 4096 27 against 35 + 24,
+// 16,384 108 against 134 + 50, 32,768 (268M ids) 349 against 264 + 99, 49,152 762 against
+// 398 + 171.
+constexpr uint32_t kSumBlocks = 32768;
 
 // SUM: partial holds the blocks' counts, and the last block writes the totals; else it
 // holds their offsets.

@@ -276,8 +276,8 @@ def test_scope_from_bytes(n, shift, torch_gpu, gs):
     np.testing.assert_array_equal(host_u32(sc, words), np.packbits(bits, bitorder="little").view(np.uint32))
 
 
-# 4096 blocks of 8192 ids are summed by the scatter itself, one more by a pass of its own
-@pytest.mark.parametrize("n", [4096 * 8192, 4096 * 8192 + 5])
+# 32,768 blocks of 8192 ids are summed by the scatter itself, one more by a pass of its own
+@pytest.mark.parametrize("n", [4096 * 8192 + 5, 32768 * 8192, 32768 * 8192 + 5])
 def test_hazard_lists_over_many_blocks(n, torch_gpu, gs):
     torch = torch_gpu
     rng = np.random.default_rng(3)
