@@ -26,27 +26,42 @@ def host_u32(t, k=None):
     return a if k is None else a[:k]
 
 
-SORT_SIZES = [1, 63, 64, 65, 128, 129, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025, 2047, 2048, 2049]
+SORT_SIZES = [1, 63, 64, 65, 128, 129, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025, 2047, 2048, 2049, 4096, 4097]
 
 
-# 256 tiles (at most two per compute unit), 1200 (more), 7500 (a block's counters cover
-# the range of its own tiles) and 37,500 (several passes over them)
-@pytest.mark.parametrize("width,height", [(256, 256), (640, 480), (1600, 1200), (4000, 2400)])
-def test_bin_sort_sizes(width, height, torch_gpu, gs):
+# 256 and 512 tiles (at most two per compute unit), 528 and 1200 (more), 7500 (a block's
+# counters cover the range of its own tiles) and 37,500 (several passes over them); every
+# depth of a tile another, runs of 2 to 9 equal ones, and one of 100 in the longer tiles
+@pytest.mark.parametrize("ties", ["none", "short", "long"])
+@pytest.mark.parametrize("width,height", [(256, 256), (512, 256), (528, 256), (640, 480), (1600, 1200), (4000, 2400)])
+def test_bin_sort_sizes(width, height, ties, torch_gpu, gs):
     torch = torch_gpu
     rng = np.random.default_rng(width)
     TX, TY = (width + 15) // 16, (height + 15) // 16
     T = TX * TY
-    tile = np.concatenate([np.full(k, t) for t, k in zip(rng.choice(T, len(SORT_SIZES), replace=False), SORT_SIZES)] +
-                          [rng.integers(0, T, 3000)]).astype(np.int64)
+    special = rng.choice(T, len(SORT_SIZES), replace=False)
+    other = np.setdiff1d(np.arange(T), special)
+    tile = np.concatenate([np.full(k, t) for t, k in zip(special, SORT_SIZES)] + [rng.choice(other, 3000)]).astype(np.int64)
     rng.shuffle(tile)
     n = tile.size
-    # a primitive covers its tile, every seventh two beside each other
+    # a primitive covers its tile, every seventh two beside each other where neither is special
     x0, y0 = tile % TX, tile // TX
-    wide = (np.arange(n) % 7 == 0) & (x0 + 1 < TX)
+    wide = (np.arange(n) % 7 == 0) & (x0 + 1 < TX) & ~np.isin(tile, special) & ~np.isin(tile + 1, special)
+    assert wide.sum() > 50
     rect = np.stack([x0, y0, x0 + 1 + wide, y0 + 1], 1).astype(np.int16)
-    depth = rng.uniform(1.0, 9.0, n).astype(np.float32)
-    depth[rng.choice(n, n // 10, replace=False)] = np.float32(2.5)
+    depth = (1.0 + rng.permutation(n) * 2.0 ** -14).astype(np.float32)
+    assert np.unique(depth).size == n
+    for t in special:
+        at = np.flatnonzero(tile == t)
+        if ties == "short":
+            k = 0
+            while k < at.size:
+                run = int(rng.integers(2, 10))
+                depth[at[k:k + run]] = depth[at[k]]
+                k += 3 * run
+        elif ties == "long" and at.size > 120:
+            depth[rng.choice(at, 100, replace=False)] = np.float32(1.5)
+    assert np.array_equal(np.bincount(np.concatenate([tile, tile[wide] + 1]), minlength=T)[special], SORT_SIZES)
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
     u32 = lambda k: torch.zeros(max(1, k), dtype=torch.int32, device="cuda")  # noqa: E731
     f = lambda *s: torch.zeros(*s, device="cuda")  # noqa: E731

@@ -500,7 +500,8 @@ def test_long_tile_lists(torch_gpu, orc):
 
 
 # (tile x, tile y, primitives, short ties, long run): one cluster per tile
-# class of the per-tile depth sort, from one wave with one key per lane up to
+# class of the per-tile depth sort (of both its forms, for few tiles and for
+# more), from one wave with one key per lane up to
 # tiles longer than a workgroup's register sort (two runs merged, 2049..4096
 # pairs) and longer than two runs (global memory).  Short ties: an eighth of
 # the primitives copy a neighbour's mean (runs of equal depth bits of a few
@@ -514,19 +515,21 @@ DEPTH_SORT_CLUSTERS = [(1, 1, 40, True, 0), (3, 1, 40, False, 0), (5, 1, 100, Tr
                        (9, 13, 4500, True, 0)]
 
 
-def test_depth_sort_paths(torch_gpu, orc):
-    """Tiles of every size class of the per-tile sort (one wave with 1, 2, 4
-    or 8 keys per lane, a workgroup up to 2048 keys, two merged runs up to
-    4096, global memory beyond), with and without pairs of equal depth bits
-    (copies of a primitive's mean): the order is exactly (tile, depth bits,
-    id) in every class."""
+@pytest.mark.parametrize("width,height", [(256, 256), (640, 480)])
+def test_depth_sort_paths(width, height, torch_gpu, orc):
+    """Tiles of every size class of the per-tile sort, with and without pairs
+    of equal depth bits (copies of a primitive's mean): the order is exactly
+    (tile, depth bits, id) in every class.  On 1200 tiles (more than two per
+    compute unit) one wave with 1, 2, 4 or 8 keys per lane, a workgroup with 8
+    up to 2048 keys, two merged runs up to 4096, global memory beyond; on 256
+    tiles one wave with 1, 2 or 4 keys per lane and a workgroup with 2, 4 or 8."""
     from paper_2607_19893_amd import scenes
     rng = np.random.default_rng(33)
     n_bg = 1500
     n = n_bg + sum(c[2] for c in DEPTH_SORT_CLUSTERS)
     w = scenes.tiny(n=n)
     sc = w.scene
-    cam = w.cameras[0]
+    cam = w.cameras[0] = scenes.look_at((0.0, 0.0, -4.0), (0.0, 0.0, 0.0), (0.0, -1.0, 0.0), width, height, 60.0)
     R = np.asarray(cam.R, np.float64)
     k = n_bg
     for tx, ty, cnt, ties, run in DEPTH_SORT_CLUSTERS:
