@@ -996,7 +996,24 @@ __device__ __forceinline__ float oct_sum(float v) {
     return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, true));
 }
 
-__device__ __forceinline__ void add_slot(float (&a)[kG], const float4& x, const float4& y, float z) {
+template <int C>
+__device__ __forceinline__ double dpp_add64(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), C, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), C, 0xF, 0xF, true);
+    return v + __hiloint2double(hi, lo);
+}
+// The sum over the wave, in all lanes.
+__device__ __forceinline__ double wave_sum64(double v) {
+    v = dpp_add64<0xB1>(v);         // quads, 8 lanes, rows of 16
+    v = dpp_add64<0x4E>(v);
+    v = dpp_add64<0x141>(v);
+    v = dpp_add64<0x140>(v);
+    v += __shfl_xor(v, 16, GS_WAVE);
+    return v + __shfl_xor(v, 32, GS_WAVE);
+}
+
+template <typename Rl>
+__device__ __forceinline__ void add_slot(Rl (&a)[kG], const float4& x, const float4& y, float z) {
     a[0] += x.x; a[1] += x.y; a[2] += x.z; a[3] += x.w;
     a[4] += y.x; a[5] += y.y; a[6] += y.z; a[7] += y.w;
     a[8] += z;
@@ -1012,7 +1029,11 @@ __device__ __forceinline__ void add_slot(float (&a)[kG], const float4& x, const 
 // consecutive primitives, whose slots share cache lines, four at a time, with one
 // lane per slot and every load of the four in flight; longer lists get one round of
 // four slots per lane more, and the rare ones beyond that are left in LDS for the
-// workgroup's waves, 256 slots a round.  Every order is fixed, so the sums do not
+// workgroup's waves, 256 slots a round and in fp64: these are the wide footprints near the
+// camera, whose geometry gradients cancel by up to 1e3, so that the order of an fp32 sum
+// decided the error of a whole view's gradients (over 30 seeds each, its geometric mean
+// against 64 bits fell from 3.5e-6 to 3.2e-6 on the aerial capture and from 3.1e-7 to
+// 2.8e-7 on the walk-through, for 0.3 to 0.7 us).  Every order is fixed, so the sums do not
 // depend on scheduling.  A thread per primitive with lists of more than 8 slots taken
 // whole by the wave one after the other, before, and this: 200k ring at 720p (6 slots
 // a primitive on average) 51 -> 18 us, 1M room 58 -> 37, 3M walk-through (2 slots)
@@ -1100,7 +1121,7 @@ __global__ void __launch_bounds__(GS_BLOCK) k_slot_sum(const uint32_t* __restric
     __syncthreads();
     for (uint32_t l = threadIdx.x / GS_WAVE; l < s_n; l += GS_BLOCK / GS_WAVE) {
         const uint3 e = s_long[l];
-        float a[kG] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+        double a[kG] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
         for (uint32_t k0 = 0; k0 < e.z; k0 += 4 * GS_WAVE) {
             float4 x[4][2];
             float x8[4];
@@ -1116,13 +1137,14 @@ __global__ void __launch_bounds__(GS_BLOCK) k_slot_sum(const uint32_t* __restric
             for (int j = 0; j < 4; ++j)
                 if (k0 + j * GS_WAVE + lane < e.z) add_slot(a, x[j][0], x[j][1], x8[j]);
         }
+        float f[kG];
 #pragma unroll
-        for (int q = 0; q < kG; ++q) a[q] = wave_sum(a[q]);
+        for (int q = 0; q < kG; ++q) f[q] = (float)wave_sum64(a[q]);
         if (lane == 0) {
             float4* dst = reinterpret_cast<float4*>(sums + (size_t)e.x * kSlot);
-            dst[0] = make_float4(a[0], a[1], a[2], a[3]);
-            dst[1] = make_float4(a[4], a[5], a[6], a[7]);
-            dst[2] = make_float4(a[8], 0.0f, 0.0f, 0.0f);
+            dst[0] = make_float4(f[0], f[1], f[2], f[3]);
+            dst[1] = make_float4(f[4], f[5], f[6], f[7]);
+            dst[2] = make_float4(f[8], 0.0f, 0.0f, 0.0f);
         }
     }
 }
