@@ -268,7 +268,10 @@ gs_status gs_bin_sort(const gs_proj* proj, int32_t n, const uint32_t* vis_idx, c
  *   pair_stats [4] uint64 or NULL (accumulated: zero it before the call):
  *   += number of (pixel, pair) evaluations, of included pairs, of (row, pair)
  *   steps the kernel executed (a row is the 16 pixels of one 16-lane row of a
- *   wave), and of those steps in which at least one pixel included the pair
+ *   wave; a wave takes a pair with its four rows together, so each of its steps
+ *   counts four, rows that the pair does not reach included), and of those steps
+ *   in which at least one pixel included the pair.  The third and fourth describe
+ *   the kernel's work, not the image, and change with its form
  *   bg: 3 floats on the HOST
  *   tile_order [T] uint32 or NULL: the order in which workgroups take the
  *   tiles (gs_bin_sort's tile_order, any permutation of 0..T-1, or NULL for

@@ -369,8 +369,15 @@ __device__ __forceinline__ uint32_t tile_order_key(uint32_t n) {
 // keys above long_key, and the dispatch order puts all others first.  Where the tiles
 // leave most of the chip idle (FEW, at most two per compute unit) a tile's own time
 // counts: its waves share it from 256 pairs on, with as few keys a lane as hold it
-// (256 tiles with one of 598 pairs: 15.8 -> 11.7 us, 475 tiles 17.4 -> 11.8).  With
-// more tiles the longer code and the barriers cost more (8160 tiles: 30 -> 35 us).
+// (256 tiles with one of 598 pairs: 15.8 -> 11.7 us).  With many tiles the longer code
+// and the barriers cost more (8160 tiles of a 1M room: 30 -> 35 us).  In between it is
+// the pairs a tile that decide, not known to the host.  Measured on a ring of 20k, 60k
+// and 150k primitives (65k, 137k and 270k pairs on 475 tiles, 273k, 467k and 762k on
+// 3600), the other form -> FEW: 475 tiles 18.4 -> 12.2, 22.7 -> 23.3, 108 -> 108 us; 578
+// tiles 18.2 -> 11.1, 21.6 -> 22.1, 82.5 -> 82.1; 1900 tiles 16.6 -> 10.6, 19.0 -> 20.4,
+// 24.9 -> 25.4; 3600 tiles 16.0 -> 9.9, 19.5 -> 15.4, 28.3 -> 25.6.  The line is at the
+// lower end, below which the chip has idle units whatever the tiles hold; up to a few
+// thousand tiles FEW would mostly gain too, and lost 7% at worst here.
 template <bool FEW>
 constexpr uint32_t kWaveSortMax = FEW ? 256u : 512u;
 template <bool FEW>
@@ -1102,8 +1109,9 @@ __device__ __forceinline__ void sort_long_tile(uint32_t t, uint32_t start, uint3
 
 // Per-tile depth sort, a persistent grid over the dispatch records.  The
 // first n_long records (kWaveSortMax<FEW> pairs or more) go to whole workgroups,
-// records b, b + G, .. to workgroup b; then every wave takes the remaining
-// records from the shortest up, records T-1-s for s = 4b + w, 4b + w + 4G, ..
+// records b, b + G, .. to workgroup b; then the waves take the rest, longest first,
+// dealt out from the workgroup behind the last long tile's on: wave w of workgroup b
+// records n_long + s for s = 4 ((b - n_long) mod G) + w and on in steps of 4G.
 // Output: the tiles' pairs ordered by (depth bits, emission position), with
 // the primitive ids, the sorted -> emission map and the optional 64-bit keys.
 template <bool FEW>

@@ -16,7 +16,7 @@
 // over each 16-lane row with DPP, stored in the strip's LDS record of the pair,
 // combined over the strips in a fixed order, and written to the pair's slot at its
 // emission position (a primitive's pairs side by side).  Per visible primitive,
-// k_slot_sum adds its slots in order -- deterministic, no floating-point atomics
+// k_slot_sum adds its slots in a fixed order -- deterministic, no floating-point atomics
 // in global memory -- and k_project_bwd applies the projection and colour chain
 // rule (geometry in fp64) and writes one compact gradient row.
 #include <algorithm>
@@ -222,12 +222,12 @@ __device__ __forceinline__ uint32_t dispatch_tile(const uint32_t* __restrict__ t
 __device__ __forceinline__ int quad_x(int tid) { return ((tid >> 6) & 1) * 8 + (tid & 7); }
 __device__ __forceinline__ int quad_y(int tid) { return (tid >> 7) * 8 + ((tid >> 3) & 7); }
 
-// What bounds it is VALU issue: about 28 instructions per (wave, pair) step, 26 of
-// them per pixel (sigma 6, the exponential 6, blending 14).  An 8x8 block takes more
+// What bounds it is VALU issue: 27 instructions per (wave, pair) step (sigma 6, the
+// exponential 6, blending 14).  An 8x8 block takes more
 // steps than lists per 16x1 row of the tile did (their rows found 54% of the lanes
 // included, a block 34%), but a wave-uniform list needs no per-row lockstep, no list
 // building per row and no per-pair address arithmetic, and sigma as a polynomial no
-// per-pair offsets, so a step got shorter by more: 7.8e7 -> 5.4e7 VALU a view on a
+// per-pair offsets, so a step got shorter by more: 7.8e7 -> 6.4e7 VALU a view on a
 // 1M-primitive 1080p room.  Four pairs an iteration keep four records' loads and
 // footprints in flight beside the serial T chain; their registers allow six waves per
 // SIMD, which measured better than two pairs at eight waves, most of all where few tiles
@@ -507,8 +507,10 @@ constexpr int kSums = 8;              // floats a strip keeps per pair
 // (m_x, m_y, m_xx, m_xy, m_yy, m, colour); k_project_bwd expands it with the
 // conic once per primitive.
 //
-// What bounds it is VALU issue: 55 instructions per (wave, pair) step, 24 of them for
-// the eight sums.  The strip is 8x2 because it weighs the steps against the sums:
+// What bounds it is VALU issue: 53 instructions per (wave, pair) step, 18 of them for
+// the eight sums (24 while they held ds h and ds dx h, h the pixel row's offset from the
+// strip's middle, which also cost the y moments their last bits).  Two pairs are
+// evaluated side by side in front of the serial T and gS chain.  The strip is 8x2 because it weighs the steps against the sums:
 // 16x1 rows need six sums but 1.26 times the steps, 4x4 blocks nine for 0.93 times, 8x8
 // blocks nine over 64 lanes for 1.33 times.  The sums are DPP additions because nothing
 // else here is cheaper: the 32-bit matrix product does not run beside other waves' VALU
@@ -516,8 +518,8 @@ constexpr int kSums = 8;              // floats a strip keeps per pair
 // sum 64 pixels took the walk from 209 to 293 us), and an LDS float add costs 3 cycles a
 // lane.  The records (33 KB) allow four workgroups per CU.  Measured, 16x1 rows with a
 // butterfly each before and this: 1M-primitive 1080p room (with the overlapped commit)
-// 264 -> 213 us, 3M walk-through 151 -> 92, 200k ring at 720p 169 -> 132, 60k ring at
-// 651x433 143 -> 80, 10k box at 256x256 82 -> 46.
+// 264 -> 208 us, 3M walk-through 151 -> 91, 200k ring at 720p 169 -> 122, 60k ring at
+// 651x433 143 -> 80, 10k box at 256x256 82 -> 45.
 
 // Eight sums over each 16-lane row, in 12 DPP additions: of m and x over each half of the
 // row, of e..h over all of it.  The halves of two of e..h are added into the two halves of
@@ -813,8 +815,8 @@ __device__ __forceinline__ void sh_basis_grad(float x, float y, float z, float* 
 
 __device__ __forceinline__ float dot3(const float* a, const float* b) { return a[0] * b[0] + a[1] * b[1] + a[2] * b[2]; }
 
-// Per-primitive work: k_project_bwd, one thread per visible row, adds the
-// primitive's pair slots and applies the chain rule.
+// Per-primitive work: k_slot_sum adds each visible primitive's pair slots, and
+// k_project_bwd, one thread per visible row, applies the chain rule to the sums.
 
 template <int DEG>
 struct RowLayout {
@@ -981,7 +983,12 @@ __device__ __forceinline__ uint32_t find_row(const uint32_t* __restrict__ u, uin
 // per lane; a primitive with more goes to a whole wave.
 constexpr uint32_t kOctSlots = 8, kOctSlots2 = 5 * kOctSlots;
 // Visible rows up to which 8 lanes take 4 primitives instead of 8, so that twice the
-// workgroups share them and one round of loads does.
+// workgroups share them and one round of loads does; with more rows the chip is full
+// either way and the workgroups' own start costs.  Measured, 4 against 8, at 2 and at 6
+// slots a primitive on average: 32k rows 4.6 against 5.9 us and 6.3 against 8.7, 98k 7.0
+// against 8.4 and 12.4 against 13.5, 131k (the line) 9.0 against 8.7 and 15.0 against
+// 14.9, 197k 12.8 against 11.0 and 19.7 against 18.8, 524k 24.0 against 21.2 and 43.2
+// against 42.7.
 constexpr uint32_t kFewRows = 1u << 17;
 
 // The value of lane I of each 8 lanes, in all of them.
