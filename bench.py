@@ -70,9 +70,9 @@ TRAFFIC = {
     "workload": "room-1M-L3-1080p",
     "id_order": "spatial",
     "sources": ["paper_2607_19893_amd/csrc/raster.hip", "paper_2607_19893_amd/csrc/binsort.hip"],
-    "code_sha256": "1a18e6d8b05dd7425179349d0a4a3ac185f7f09f5107ef08593b90e071db9e06",
-    "fetch_kib": 110512.50, "fetch_scale": 1048576.0 / 524298.7,
-    "write_kib": 91565.29, "write_scale": 1048576.0 / 1048576.0,
+    "code_sha256": "9fde720c6f16291c71aff4adf8a4ed41b607be4b9834946720708f9ebbb88709",
+    "fetch_kib": 110743.01, "fetch_scale": 1048576.0 / 524298.7,
+    "write_kib": 91553.78, "write_scale": 1048576.0 / 1048576.0,
     "profile": "profiles/k_raster_bwd-room-1M-1080p_hbm_traffic.md",
 }
 
