@@ -1009,18 +1009,41 @@ __device__ __forceinline__ double dpp_add64(double v) {
     const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), C, 0xF, 0xF, true);
     return v + __hiloint2double(hi, lo);
 }
-// The sum over the wave, in all lanes.
-__device__ __forceinline__ double wave_sum64(double v) {
-    v = dpp_add64<0xB1>(v);         // quads, 8 lanes, rows of 16
-    v = dpp_add64<0x4E>(v);
-    v = dpp_add64<0x141>(v);
-    v = dpp_add64<0x140>(v);
-    v += __shfl_xor(v, 16, GS_WAVE);
-    return v + __shfl_xor(v, 32, GS_WAVE);
+// a's halves (rows of 16 with ROWS) added in the low one (the even ones), b's in the other:
+// the swap leaves the low half of a beside that of b, and so the high halves.
+template <bool ROWS>
+__device__ __forceinline__ double swap_add64(double a, double b) {
+    const uint32_t al = __double2loint(a), ah = __double2hiint(a), bl = __double2loint(b), bh = __double2hiint(b);
+    const auto lo = ROWS ? __builtin_amdgcn_permlane16_swap(al, bl, false, false)
+                         : __builtin_amdgcn_permlane32_swap(al, bl, false, false);
+    const auto hi = ROWS ? __builtin_amdgcn_permlane16_swap(ah, bh, false, false)
+                         : __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+// The sum over each 8 lanes, in all of them.
+__device__ __forceinline__ double oct_sum64(double v) {
+    return dpp_add64<0x141>(dpp_add64<0x4E>(dpp_add64<0xB1>(v)));
+}
+// The sums of a[0..9) over the wave: returned in lane l is that of a[slot_of(l)], a8 is the
+// ninth's in all lanes.  Two values share a register from each of the first three steps on,
+// so that one step inside 8 lanes serves all eight of them.
+__device__ __forceinline__ uint32_t slot_of(uint32_t lane) {
+    return ((lane >> 5) & 1u) | ((lane >> 4) & 1u) << 1 | ((lane >> 3) & 1u) << 2;
+}
+__device__ __forceinline__ double wave_sum9(const double (&a)[kG], uint32_t lane, double& a8) {
+    const double t0 = swap_add64<true>(swap_add64<false>(a[0], a[1]), swap_add64<false>(a[2], a[3]));
+    const double t1 = swap_add64<true>(swap_add64<false>(a[4], a[5]), swap_add64<false>(a[6], a[7]));
+    const double s8 = swap_add64<false>(a[8], a[8]);
+    const double r8 = swap_add64<true>(s8, s8);
+    const bool high = (lane & 8u) != 0u;
+    const double keep = high ? t1 : t0, send = high ? t0 : t1;
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(send), 0x128, 0xF, 0xF, true);     // row_ror:8
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(send), 0x128, 0xF, 0xF, true);
+    a8 = oct_sum64(dpp_add64<0x128>(r8));
+    return oct_sum64(keep + __hiloint2double(hi, lo));
 }
 
-template <typename Rl>
-__device__ __forceinline__ void add_slot(Rl (&a)[kG], const float4& x, const float4& y, float z) {
+__device__ __forceinline__ void add_slot(float (&a)[kG], const float4& x, const float4& y, float z) {
     a[0] += x.x; a[1] += x.y; a[2] += x.z; a[3] += x.w;
     a[4] += y.x; a[5] += y.y; a[6] += y.z; a[7] += y.w;
     a[8] += z;
@@ -1036,11 +1059,14 @@ __device__ __forceinline__ void add_slot(Rl (&a)[kG], const float4& x, const flo
 // consecutive primitives, whose slots share cache lines, four at a time, with one
 // lane per slot and every load of the four in flight; longer lists get one round of
 // four slots per lane more, and the rare ones beyond that are left in LDS for the
-// workgroup's waves, 256 slots a round and in fp64: these are the wide footprints near the
-// camera, whose geometry gradients cancel by up to 1e3, so that the order of an fp32 sum
-// decided the error of a whole view's gradients (over 30 seeds each, its geometric mean
-// against 64 bits fell from 3.5e-6 to 3.2e-6 on the aerial capture and from 3.1e-7 to
-// 2.8e-7 on the walk-through, for 0.3 to 0.7 us).  Every order is fixed, so the sums do not
+// workgroup's waves, 256 slots a round: a lane's four in fp32, the lanes and rounds in fp64.
+// These are the wide footprints near the camera, whose geometry gradients cancel by up to
+// 1e3, so that the order of an fp32 sum decided the error of a whole view's gradients.  Its
+// geometric mean against 64 bits over 12 seeds each, all in fp32, all in fp64 and this: 400k
+// aerial 4.2, 3.7, 3.7e-6, 150k aerial 6.8, 5.3, 5.2e-6, 300k walk-through 7.1, 6.5, 6.5e-7.
+// The kernel on 100k primitives of an aerial capture at 1910x1400, where most lists are long:
+// 42.7, 47.4 (nine 64-bit butterflies and 36 conversions a lane), 42.2 us.
+// Every order is fixed, so the sums do not
 // depend on scheduling.  A thread per primitive with lists of more than 8 slots taken
 // whole by the wave one after the other, before, and this: 200k ring at 720p (6 slots
 // a primitive on average) 51 -> 18 us, 1M room 58 -> 37, 3M walk-through (2 slots)
@@ -1140,19 +1166,18 @@ __global__ void __launch_bounds__(GS_BLOCK) k_slot_sum(const uint32_t* __restric
                 x[j][1] = sl[1];
                 x8[j] = sl[2].x;
             }
+            float f[kG] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if (k0 + j * GS_WAVE + lane < e.z) add_slot(a, x[j][0], x[j][1], x8[j]);
-        }
-        float f[kG];
+                if (k0 + j * GS_WAVE + lane < e.z) add_slot(f, x[j][0], x[j][1], x8[j]);
 #pragma unroll
-        for (int q = 0; q < kG; ++q) f[q] = (float)wave_sum64(a[q]);
-        if (lane == 0) {
-            float4* dst = reinterpret_cast<float4*>(sums + (size_t)e.x * kSlot);
-            dst[0] = make_float4(f[0], f[1], f[2], f[3]);
-            dst[1] = make_float4(f[4], f[5], f[6], f[7]);
-            dst[2] = make_float4(f[8], 0.0f, 0.0f, 0.0f);
+            for (int q = 0; q < kG; ++q) a[q] += f[q];
         }
+        double a8;
+        const float v = (float)wave_sum9(a, lane, a8);
+        float* dst = sums + (size_t)e.x * kSlot;
+        if (at == 0u) dst[slot_of(lane)] = v;
+        if (lane == 1u) *reinterpret_cast<float4*>(dst + 8) = make_float4((float)a8, 0.0f, 0.0f, 0.0f);
     }
 }
 

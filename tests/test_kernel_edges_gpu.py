@@ -257,6 +257,10 @@ def test_slot_sums(V, torch_gpu):
     tr.pair_offset.copy_(dev(off.astype(np.int32)))
     tr.conic.copy_(dev(np.tile(np.array([1, 0, 1, 1], np.float32), (V, 1))))
     slots = rng.standard_normal((M, 12)).astype(np.float32)      # nine sums and padding per pair
+    # whole numbers in lists of more than 40 slots: four of them add up below 2^24, exactly in
+    # 32 bits, and all of a list's do not
+    long_slots = np.repeat(nt > 40, nt)
+    slots[long_slots] = rng.integers(1 << 20, 1 << 22, (long_slots.sum(), 12))
     tr.ws_bwd.view(torch.float32)[:M * 12].copy_(dev(slots.reshape(-1)))
     tr.raster_bwd_project(grad2d=True)
     torch.cuda.synchronize()
@@ -266,7 +270,8 @@ def test_slot_sums(V, torch_gpu):
     err = np.abs(tr.grad2d.cpu().numpy()[:V] - s * scale)
     # at most 4 + 8 + 6 additions in a row per value, each 2^-24 of the summed magnitudes
     assert (err <= 20 * 2.0 ** -24 * mag * np.abs(scale) + 1e-12).all()
-    # lists of more than 40 slots are summed in 64 bits and rounded once
+    # lists of more than 40 slots: four of a lane's in 32 bits, which is exact here, the rest in
+    # 64 bits, rounded once
     many = nt > 40
     assert (err <= 1.001 * 2.0 ** -24 * np.abs(s * scale) + 1e-12)[many].all()
 
