@@ -70,9 +70,9 @@ TRAFFIC = {
     "workload": "room-1M-L3-1080p",
     "id_order": "spatial",
     "sources": ["paper_2607_19893_amd/csrc/raster.hip", "paper_2607_19893_amd/csrc/binsort.hip"],
-    "code_sha256": "9fde720c6f16291c71aff4adf8a4ed41b607be4b9834946720708f9ebbb88709",
-    "fetch_kib": 110743.01, "fetch_scale": 1048576.0 / 524298.7,
-    "write_kib": 91553.78, "write_scale": 1048576.0 / 1048576.0,
+    "code_sha256": "082e9d9469551540424c94fb719785d3e4107e1328e877dfda84c6051a15c3b7",
+    "fetch_kib": 110723.35, "fetch_scale": 1048576.0 / 524298.5,
+    "write_kib": 91553.47, "write_scale": 1048576.0 / 1048576.0,
     "profile": "profiles/k_raster_bwd-room-1M-1080p_hbm_traffic.md",
 }
 
